@@ -74,15 +74,18 @@ hipError_t launch_extend(const ExtendParams& p, int head_dim, int page_size, boo
 constexpr int kMaxDevices = 64;
 constexpr int kStagingSlots = 8;
 // Every staging slot has this fixed size, allocated once per device (cw_init or
-// the first call that uploads a plan); a plan larger than a slot is rejected.
-constexpr size_t kStagingSlotBytes = size_t(4) << 20;
+// the first call that uploads a plan).  A plan whose size before levelling is more
+// than kMaxPlanBytes is rejected; levelling adds at most kLevelMetaBytes.
 // The last bytes of a slot are the words its upload kernel's workgroups write
 // once they have read the slot (one per workgroup); the plan gets the rest.
 constexpr size_t kDoneBytes = size_t(kMaxUploadWorkgroups) * sizeof(uint32_t);
-constexpr size_t kPlanSlotBytes = kStagingSlotBytes - kDoneBytes;
+constexpr size_t kMaxPlanBytes = (size_t(4) << 20) - kDoneBytes;
+constexpr size_t kPlanSlotBytes = kMaxPlanBytes + kLevelMetaBytes;
+constexpr size_t kStagingSlotBytes = kPlanSlotBytes + kDoneBytes;
 // A call captured into a graph carries its plan in kernel arguments (2 KiB per
-// copy launch); its plan may take at most this many bytes.
+// copy launch); its plan may take at most this many bytes before levelling.
 constexpr size_t kCaptureMaxBytes = size_t(256) << 10;
+constexpr size_t kCaptureBufBytes = kCaptureMaxBytes + kLevelMetaBytes;
 
 struct StagingSlot {
   void* host = nullptr;
@@ -102,7 +105,7 @@ struct DeviceState {
   bool ready = false;     // staging ring allocated
   StagingSlot slots[kStagingSlots];
   int next_slot = 0;
-  uint8_t* capture_buf = nullptr;  // kCaptureMaxBytes of host memory: plans of captured calls
+  uint8_t* capture_buf = nullptr;  // kCaptureBufBytes of host memory: plans of captured calls
   uint32_t upload_seq = 0;         // the last value handed to an upload kernel
   uint8_t* scratch = nullptr;  // this device's copy of the static scratch array (cw_init)
 };
@@ -160,7 +163,7 @@ cw_status_t init_locked(DeviceState& st) {
     delete[] st.capture_buf;
     st.capture_buf = nullptr;
   };
-  st.capture_buf = new (std::nothrow) uint8_t[kCaptureMaxBytes];
+  st.capture_buf = new (std::nothrow) uint8_t[kCaptureBufBytes];
   if (st.capture_buf == nullptr) return fail(CW_ERR_UNSUPPORTED, "host memory for captured plans");
   for (; made < kStagingSlots; ++made) {
     StagingSlot& s = st.slots[made];
@@ -200,7 +203,8 @@ cw_status_t current_state(DeviceState** out) {
 // Stages `bytes` of host data for `stream` in a pinned staging slot, so that the
 // caller's host buffer can be reused at once, and enqueues the kernels that read
 // it: `fill(host)` writes the bytes into the slot (the plan is packed there
-// directly, without an intermediate buffer), then `launch(base)` enqueues the
+// directly, without an intermediate buffer; `whole_bytes` is its size before
+// levelling, which the limits apply to), then `launch(base)` enqueues the
 // kernels, with `base` the device address they read the data at.  Copy mode:
 // a small kernel copies the slot to `dst` (device memory) and base = dst.
 // Direct mode: the kernels read the slot itself over the host link (base = the
@@ -286,7 +290,7 @@ cw_status_t wait_slot_reads(StagingSlot& s) {
 }
 
 template <class Fill, class Launch, class FillHead>
-cw_status_t stage_and_launch(size_t bytes, void* dst, hipStream_t stream, Fill&& fill,
+cw_status_t stage_and_launch(size_t bytes, size_t whole_bytes, void* dst, hipStream_t stream, Fill&& fill,
                              Launch&& launch, bool no_alloc, bool direct,
                              const CompactUpload* compact, FillHead&& fill_head, bool arg_plan = false) {
   if (bytes == 0) return launch(static_cast<const uint8_t*>(dst), nullptr);
@@ -309,11 +313,11 @@ cw_status_t stage_and_launch(size_t bytes, void* dst, hipStream_t stream, Fill&&
       return launch(nullptr, &ap);
     }
   }
-  if (bytes > kPlanSlotBytes)
+  if (whole_bytes > kMaxPlanBytes || bytes > kPlanSlotBytes)
     return fail(CW_ERR_UNSUPPORTED,
                 "the call's plan takes %zu bytes, more than the %zu-byte staging slot "
                 "(too many sequences or work items for one call)",
-                bytes, kPlanSlotBytes);
+                whole_bytes, kMaxPlanBytes);
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   hipError_t ce = hipStreamIsCapturing(stream, &capture);
   if (ce != hipSuccess) return hip_fail(ce, "hipStreamIsCapturing");
@@ -324,12 +328,17 @@ cw_status_t stage_and_launch(size_t bytes, void* dst, hipStream_t stream, Fill&&
   std::lock_guard<std::mutex> g(st.staging_mu);
   if (capture != hipStreamCaptureStatusNone) {
     if (capture != hipStreamCaptureStatusActive) return fail(CW_ERR_HIP, "the stream's capture has been invalidated");
-    if (!st.ready) return fail(CW_ERR_INIT, "cw_init() must be called on this device before capturing a call");
-    if (bytes > kCaptureMaxBytes || bytes % 4 != 0)
-      return fail(CW_ERR_UNSUPPORTED, "a captured call's plan takes %zu bytes, more than %zu", bytes,
+    // (a plan that only levelling made too large for the kernel arguments needs no set-up)
+    if (!st.ready && !(arg_plan && !direct && whole_bytes <= kArgPlanBytes))
+      return fail(CW_ERR_INIT, "cw_init() must be called on this device before capturing a call");
+    if (whole_bytes > kCaptureMaxBytes || bytes > kCaptureBufBytes || bytes % 4 != 0)
+      return fail(CW_ERR_UNSUPPORTED, "a captured call's plan takes %zu bytes, more than %zu", whole_bytes,
                   kCaptureMaxBytes);
-    fill(st.capture_buf);
-    ce = launch_arg_copy(st.capture_buf, dst, bytes, stream);
+    std::vector<uint8_t> own;
+    if (!st.ready) own.resize(bytes);
+    uint8_t* buf = st.ready ? st.capture_buf : own.data();
+    fill(buf);
+    ce = launch_arg_copy(buf, dst, bytes, stream);
     if (ce != hipSuccess) return hip_fail(ce, "plan upload kernel launch");
     return launch(static_cast<const uint8_t*>(dst), nullptr);
   }
@@ -382,7 +391,7 @@ cw_status_t stage_and_launch(size_t bytes, void* dst, hipStream_t stream, Fill&&
 
 template <class Fill>
 cw_status_t upload_fill(size_t bytes, void* dst, hipStream_t stream, Fill&& fill) {
-  return stage_and_launch(bytes, dst, stream, fill, [](const uint8_t*, const ArgPlan*) { return CW_OK; },
+  return stage_and_launch(bytes, bytes, dst, stream, fill, [](const uint8_t*, const ArgPlan*) { return CW_OK; },
                           false, false, nullptr, fill);
 }
 
@@ -713,7 +722,7 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
     return CW_OK;
   };
   const bool arg_plan = arg_plans() && (decode ? compact && compact_arg_fits(cu) : true);
-  return stage_and_launch(plan.meta_bytes, ws, stream, [&](uint8_t* h) { pack_plan_meta(plan, h); },
+  return stage_and_launch(plan.meta_bytes, plan.whole_meta_bytes, ws, stream, [&](uint8_t* h) { pack_plan_meta(plan, h); },
                           launch, no_alloc, plan_direct(no_alloc), compact ? &cu : nullptr,
                           [&](uint8_t* h) { pack_plan_head(plan, h); }, arg_plan);
 }
@@ -936,7 +945,8 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
   };
   const bool arg_plan =
       arg_plans() && (sp.dec.empty() || (sp.ext.empty() && compact && compact_arg_fits(cu)));
-  return stage_and_launch(sp.meta_bytes, ws, stream, [&](uint8_t* h) {
+  return stage_and_launch(sp.meta_bytes, sp.meta_bytes - sp.ext_plan.meta_bytes + sp.ext_plan.whole_meta_bytes, ws,
+                          stream, [&](uint8_t* h) {
     head(h);
     if (!sp.dec.empty()) pack_plan_meta(sp.dec_plan, h + sp.off_dec_meta);
   }, launch, false, plan_direct(false), compact ? &cu : nullptr, [&](uint8_t* h) {

@@ -7,6 +7,8 @@
 // equal length ("split-K"); the chunks write unnormalised partials that a
 // second kernel merges with a log-sum-exp weighting.
 //
+// A plan whose workgroups would still finish far apart is levelled (level_plan).
+//
 // Launch order is XCD-aware: the dispatcher hands workgroup i to XCD i % X, and
 // each XCD has its own L2.  All tiles of one (sequence, kv head) read the same
 // keys, so the work of a (sequence, kv head) that fills whole rounds of the GPU
@@ -31,15 +33,362 @@ constexpr int32_t MIN_CHUNK_TILES = 4;  // a chunk of fewer keys wastes the Q lo
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Tile {
-  int32_t seq, kvh, q_row0, rows, kv_len, n_kt;
+  int32_t seq, kvh, q_row0, rows, kv_len, n_kt, n_pre;  // n_pre: key tiles wholly in the prefix
 };
 
+// Work of one (sequence, kv head), or a share of it: items [first, first + n) of
+// the plan's items in bundle order.
 struct Bundle {
-  std::vector<WorkItem> items;
+  int64_t first = 0, n = 0;
   int64_t cost = 0;  // key tiles
 };
 
+int64_t key_tiles(const WorkItem& w) { return (w.kv_end - w.kv_begin + BLOCK_N - 1) / BLOCK_N; }
+
 void layout_workspace(ExtendPlan& plan, int32_t head_dim);
+
+size_t plan_meta_bytes(size_t n_seqs, size_t n_items, size_t n_groups) {
+  return align256(align256(align256(n_seqs * sizeof(SeqInfo)) + n_items * sizeof(WorkItem)) +
+                  n_groups * sizeof(CombineGroup));
+}
+
+// Entries of the launch list made of these queues: they are interleaved, short ones
+// padded with idle items, without trailing idle items (one used queue: as it is).
+template <class T>
+size_t launch_count(const std::vector<std::vector<T>>& queues) {
+  size_t longest = 0, last = 0, used = 0;
+  for (size_t x = 0; x < queues.size(); ++x) {
+    used += queues[x].empty() ? 0 : 1;
+    if (queues[x].size() >= longest) {
+      longest = queues[x].size();
+      last = x;
+    }
+  }
+  return used > 1 ? (longest - 1) * queues.size() + last + 1 : longest;
+}
+
+// ---- levelled plans -------------------------------------------------------
+// The cost model, in hundredths of the time one workgroup takes for a prefix
+// key tile when all its rows are in use (1.7-2.2 us at head dim 128).  Fewer
+// rows make a tile cheaper only down to the time its K/V take to arrive
+// (measured per tile, 256 workgroups, unshared K/V: 2.19 us with 256 rows, 1.94
+// with 192, 1.58 with 128, 1.53 with 32).
+constexpr int64_t kItemCost = 300;       // start-up and epilogue of a work item
+constexpr int64_t kMergeCost = 450;      // the merge kernel's launch and latency
+constexpr int64_t kMergePartCost = 2;    // per partial slot merged
+constexpr int64_t kMinGap = MIN_CHUNK_TILES * 100 + kItemCost;
+// What cutting tiles has to gain at least (about 55 us): calls of 20-100 us lost
+// 5-60 us to the merge and the larger plan when they were levelled.
+constexpr int64_t kMinCutGain = 3000;
+
+int64_t row_rate(int32_t rows) {
+  constexpr int64_t rate[8] = {72, 72, 72, 72, 80, 89, 95, 100};
+  return rate[std::min(7, (rows - 1) / 32)];
+}
+
+// Key tiles [a, b) of a query tile.
+int64_t span_cost(const Tile& t, int64_t a, int64_t b, int64_t suffix_weight) {
+  const int64_t pre = std::max<int64_t>(0, std::min<int64_t>(b, t.n_pre) - a), suf = (b - a) - pre;
+  return (pre * 100 + suf * suffix_weight) * row_rate(t.rows) / 100;
+}
+int64_t tile_cost(const Tile& t, int64_t suffix_weight) {
+  return kItemCost + span_cost(t, 0, t.n_kt, suffix_weight);
+}
+// The last key tile up to which the tiles from `a` on cost at most `budget`.
+int64_t span_end(const Tile& t, int64_t a, int64_t budget, int64_t suffix_weight) {
+  const int64_t units = std::max<int64_t>(0, budget) * 100 / row_rate(t.rows);
+  const int64_t pre = std::max<int64_t>(0, t.n_pre - a);
+  if (units < pre * 100) return a + units / 100;
+  return a + pre + (units - pre * 100) / suffix_weight;
+}
+
+// Workgroup slots by the time they are free: a binary heap, soonest first.
+struct Slots {
+  struct Slot {
+    int64_t t;
+    int32_t r;
+    bool operator<(const Slot& o) const { return t != o.t ? t < o.t : r < o.r; }
+  };
+  std::vector<Slot> s;
+  explicit Slots(int64_t R) : s(static_cast<size_t>(R)) {
+    for (int64_t r = 0; r < R; ++r) s[r] = Slot{0, static_cast<int32_t>(r)};
+  }
+  int64_t soonest() const { return s[0].t; }
+  void take(int64_t cost) {  // the soonest slot runs for `cost` more
+    Slot v = s[0];
+    v.t += cost;
+    size_t i = 0;
+    for (;;) {
+      size_t c = 2 * i + 1;
+      if (c >= s.size()) break;
+      if (c + 1 < s.size() && s[c + 1] < s[c]) ++c;
+      if (!(s[c] < v)) break;
+      s[i] = s[c];
+      i = c;
+    }
+    s[i] = v;
+  }
+  int64_t latest() const {
+    int64_t m = 0;
+    for (const Slot& v : s) m = std::max(m, v.t);
+    return m;
+  }
+};
+
+// The time at which the last of R slots finishes when the items (their costs in
+// launch order) each go to the slot that is free first.
+int64_t list_makespan(const std::vector<int64_t>& costs, int64_t R) {
+  Slots sl(R);
+  for (const int64_t c : costs) sl.take(c);
+  return sl.latest();
+}
+
+struct Piece {  // key tiles [k0, k1) of tile `tile`, planned to start at `start`
+  int32_t tile, k0, k1;
+  int64_t start;
+};
+struct Left {  // a tile not placed yet, from key tile k0 on
+  int32_t tile, k0;
+};
+
+// Fills the slots (in order of the time they are free) up to `level` with `left`
+// in pieces of key ranges; returns the entries used up.
+size_t fill_slots(const std::vector<Tile>& tiles, std::vector<Left>& left, std::vector<Slots::Slot>& slots,
+                  size_t& next, int64_t level, int64_t wgt, std::vector<Piece>& out) {
+  size_t i = 0;
+  while (i < left.size() && next < slots.size()) {
+    Slots::Slot& sl = slots[next];
+    Left& l = left[i];
+    const Tile& t = tiles[l.tile];
+    const int64_t gap = level - sl.t;
+    const int64_t whole = kItemCost + span_cost(t, l.k0, t.n_kt, wgt);
+    if (whole <= gap) {
+      out.push_back(Piece{l.tile, l.k0, t.n_kt, sl.t});
+      sl.t += whole;
+      ++i;
+      continue;
+    }
+    if (gap >= kMinGap) {
+      const int64_t e = std::min<int64_t>(span_end(t, l.k0, gap - kItemCost, wgt), t.n_kt - MIN_CHUNK_TILES);
+      if (e - l.k0 >= MIN_CHUNK_TILES) {
+        out.push_back(Piece{l.tile, l.k0, static_cast<int32_t>(e), sl.t});
+        l.k0 = static_cast<int32_t>(e);
+      }
+    }
+    ++next;
+  }
+  return i;
+}
+
+// Spreads the tiles over the queues so that each queue's R slots finish by
+// `level`: a queue takes whole tiles in the order of `owned` while they end by
+// `level`; what is left fills the slots in pieces of key ranges, its own queue's
+// slots first.  Returns false if something does not fit.
+bool level_queues(const std::vector<Tile>& tiles, const std::vector<std::vector<int32_t>>& owned,
+                  const std::vector<bool>& as_before, int64_t wgt, int64_t R, int64_t level,
+                  std::vector<std::vector<Piece>>& queues) {
+  const size_t X = owned.size();
+  std::vector<std::vector<Slots::Slot>> slots(X);
+  std::vector<std::vector<Left>> left(X);
+  std::vector<int32_t> pos(tiles.size());  // of a tile in its queue's `owned`
+  std::vector<size_t> next(X, 0);
+  queues.assign(X, {});
+  for (size_t x = 0; x < X; ++x) {
+    for (size_t i = 0; i < owned[x].size(); ++i) pos[owned[x][i]] = static_cast<int32_t>(i);
+    if (as_before[x]) {  // the same costs as the queue before: the same pieces of its own tiles
+      slots[x] = slots[x - 1];
+      next[x] = next[x - 1];
+      for (const Piece& p : queues[x - 1])
+        queues[x].push_back(Piece{owned[x][pos[p.tile]], p.k0, p.k1, p.start});
+      for (const Left& l : left[x - 1]) left[x].push_back(Left{owned[x][pos[l.tile]], l.k0});
+      continue;
+    }
+    Slots heap(R);
+    for (const int32_t ti : owned[x]) {
+      const int64_t c = tile_cost(tiles[ti], wgt);
+      if (heap.soonest() + c > level) {
+        left[x].push_back(Left{ti, 0});
+        continue;
+      }
+      queues[x].push_back(Piece{ti, 0, tiles[ti].n_kt, heap.soonest()});
+      heap.take(c);
+    }
+    slots[x] = std::move(heap.s);
+    std::sort(slots[x].begin(), slots[x].end());
+    const size_t used = fill_slots(tiles, left[x], slots[x], next[x], level, wgt, queues[x]);
+    left[x].erase(left[x].begin(), left[x].begin() + static_cast<std::ptrdiff_t>(used));
+  }
+  std::vector<Left> rest;
+  for (size_t x = 0; x < X; ++x) rest.insert(rest.end(), left[x].begin(), left[x].end());
+  for (size_t x = 0; x < X && !rest.empty(); ++x) {
+    const size_t used = fill_slots(tiles, rest, slots[x], next[x], level, wgt, queues[x]);
+    rest.erase(rest.begin(), rest.begin() + static_cast<std::ptrdiff_t>(used));
+  }
+  return rest.empty();
+}
+
+// Replaces `queues` (work items per XCD in launch order) and the plan's merge
+// groups where the workgroups of the plan as it is would finish far apart:
+//  - by whole tiles in another order, bundles with the longest tiles first, so
+//    that short tiles are left for the end (where a bundle's own tiles differ by
+//    more than half, as without a cached prefix, its longest tiles first);
+//  - or by that order cut off at a common level, the rest cut into key ranges that
+//    fill every slot up to it.  The cuts of a bundle's tiles lie at different
+//    keys, so their workgroups share less of the K/V in their XCD's L2: hence
+//    whole tiles wherever they fit.
+// Measured: 7 turns of 383-3506 tokens 7.90 -> 6.88 ms, 32 chunks + 32 decodes
+// 4.16 -> 4.03 ms, a mixed fp8 step 5.53 -> 5.34 ms, 10 replies of 12-600 tokens
+// 744 -> 686 us, 4 prompts of 2-6k tokens without a prefix 365 -> 343 us (order
+// alone).  The gain is about half of what the model says: workgroups that share
+// the chip with idle CUs run faster.
+void level_plan(ExtendPlan& plan, const std::vector<Tile>& tiles, const std::vector<Bundle>& whole_bundles,
+                int64_t wgt, int64_t R, int32_t head_dim, std::vector<std::vector<WorkItem>>& queues) {
+  const size_t X = queues.size();
+  if (tiles.empty() || tiles.size() > size_t(kMaxLevelTiles)) return;
+
+  // the plan as it is
+  int64_t now = 0, sum = 0;
+  {
+    std::vector<int64_t> costs, last;
+    int64_t last_span = 0;
+    for (const auto& q : queues) {
+      costs.clear();
+      for (const WorkItem& w : q) {
+        Tile t{};
+        t.rows = w.rows;
+        t.n_pre = plan.seqs[w.seq].lp / BLOCK_N;
+        costs.push_back(kItemCost + span_cost(t, w.kv_begin / BLOCK_N, (w.kv_end + BLOCK_N - 1) / BLOCK_N, wgt));
+        sum += costs.back();
+      }
+      if (costs != last) {
+        last_span = list_makespan(costs, R);
+        last.swap(costs);
+      }
+      now = std::max(now, last_span);
+    }
+  }
+  if (plan.n_parts > 0) now += kMergeCost + kMergePartCost * plan.n_parts;
+  const int64_t slots = static_cast<int64_t>(X) * R;
+  if (sum / slots * 103 >= now * 100) return;
+
+  // bundles to queues: largest first to the least loaded queue; then, in a queue,
+  // bundles with the longest tiles first
+  struct Bd {
+    int32_t t0, n;
+    int64_t cost, longest, shortest;
+  };
+  std::vector<Bd> bundles;
+  bundles.reserve(whole_bundles.size());
+  int64_t total = 0;
+  for (const Bundle& wb : whole_bundles) {
+    Bd bd{static_cast<int32_t>(wb.first), static_cast<int32_t>(wb.n), 0, 0, INT64_MAX};
+    for (int32_t i = bd.t0; i < bd.t0 + bd.n; ++i) {
+      const int64_t c = tile_cost(tiles[i], wgt);
+      bd.cost += c;
+      bd.longest = std::max(bd.longest, c);
+      bd.shortest = std::min(bd.shortest, c);
+    }
+    total += bd.cost;
+    bundles.push_back(bd);
+  }
+  std::stable_sort(bundles.begin(), bundles.end(), [](const Bd& a, const Bd& c) { return a.cost > c.cost; });
+  std::vector<std::vector<const Bd*>> mine(X);
+  std::vector<int64_t> load(X, 0);
+  for (const Bd& bd : bundles) {
+    const size_t x = static_cast<size_t>(std::min_element(load.begin(), load.end()) - load.begin());
+    load[x] += bd.cost;
+    mine[x].push_back(&bd);
+  }
+  std::vector<std::vector<int32_t>> owned(X);
+  std::vector<bool> as_before(X, false);  // queue x has the same costs in the same order as queue x - 1
+  std::vector<int64_t> costs, last;
+  int64_t ordered = 0, last_span = 0;
+  for (size_t x = 0; x < X; ++x) {
+    std::stable_sort(mine[x].begin(), mine[x].end(),
+                     [](const Bd* a, const Bd* c) { return a->longest > c->longest; });
+    costs.clear();
+    for (const Bd* bd : mine[x]) {
+      const bool reverse = bd->shortest * 2 < bd->longest;
+      for (int32_t i = 0; i < bd->n; ++i) {
+        owned[x].push_back(reverse ? bd->t0 + bd->n - 1 - i : bd->t0 + i);
+        costs.push_back(tile_cost(tiles[owned[x].back()], wgt));
+      }
+    }
+    as_before[x] = x > 0 && costs == last;
+    if (!as_before[x]) {
+      last_span = list_makespan(costs, R);
+      last.swap(costs);
+    }
+    ordered = std::max(ordered, last_span);
+  }
+  const bool reorder = ordered * 104 < now * 100;
+  const int64_t best = reorder ? ordered : now;
+
+  // the lowest level that holds everything (each cut adds an item's own cost)
+  std::vector<std::vector<Piece>> pieces;
+  std::vector<int32_t> n_of(tiles.size(), 1);
+  const int64_t base = (total + slots - 1) / slots;
+  bool cut = false;
+  if ((base + kMergeCost) * 103 < best * 100 && best - base - kMergeCost >= kMinCutGain) {
+    int64_t level = 0;
+    for (int64_t k = 1; k <= 6 && !cut; ++k) {
+      level = base + k * (base / 100 + kItemCost / 4);
+      cut = level_queues(tiles, owned, as_before, wgt, R, level, pieces);
+    }
+    if (cut) {
+      std::fill(n_of.begin(), n_of.end(), 0);
+      for (const auto& q : pieces)
+        for (const Piece& p : q) ++n_of[p.tile];
+      int64_t n_parts = 0;
+      for (const int32_t n : n_of) n_parts += n > 1 ? n : 0;
+      const int64_t then = level + kMergeCost + kMergePartCost * n_parts;
+      const int64_t slot_bytes = int64_t(plan.part_rows) * (head_dim * 2 + 8);
+      cut = then * 103 < best * 100 && best - then >= kMinCutGain && n_parts * slot_bytes <= kLevelPartBytes;
+    }
+  }
+  if (!cut && !reorder) return;
+  if (!cut) {
+    std::fill(n_of.begin(), n_of.end(), 1);
+    pieces.assign(X, {});
+    for (size_t x = 0; x < X; ++x)
+      for (const int32_t ti : owned[x]) pieces[x].push_back(Piece{ti, 0, tiles[ti].n_kt, 0});
+  }
+  size_t n_groups = 0;
+  for (const int32_t n : n_of) n_groups += n > 1 ? 1 : 0;
+  if (plan_meta_bytes(plan.seqs.size(), launch_count(pieces), n_groups) > plan.whole_meta_bytes + kLevelMetaBytes) return;
+
+  // partial slots: a tile's pieces in key order
+  plan.groups.clear();
+  plan.n_parts = 0;
+  std::vector<int32_t> part0(tiles.size(), -1);
+  for (size_t i = 0; i < tiles.size(); ++i) {
+    if (n_of[i] < 2) continue;
+    const Tile& t = tiles[i];
+    part0[i] = static_cast<int32_t>(plan.n_parts);
+    plan.groups.push_back(CombineGroup{t.seq, t.kvh, t.q_row0, t.rows, part0[i], n_of[i], 0, 0});
+    plan.n_parts += n_of[i];
+  }
+  std::vector<std::pair<int32_t, int32_t>> cuts;  // (tile, first key tile) of the pieces of cut tiles
+  for (const auto& q : pieces)
+    for (const Piece& p : q)
+      if (n_of[p.tile] > 1) cuts.emplace_back(p.tile, p.k0);
+  std::sort(cuts.begin(), cuts.end());  // in tile order: a tile's first entry is at its part0
+  for (size_t x = 0; x < X; ++x) {
+    std::stable_sort(pieces[x].begin(), pieces[x].end(),
+                     [](const Piece& a, const Piece& c) { return a.start < c.start; });
+    queues[x].clear();
+    queues[x].reserve(pieces[x].size());
+    for (const Piece& p : pieces[x]) {
+      const Tile& t = tiles[p.tile];
+      int32_t part = -1;
+      if (n_of[p.tile] > 1)
+        part = static_cast<int32_t>(std::lower_bound(cuts.begin() + part0[p.tile], cuts.end(),
+                                                     std::make_pair(p.tile, p.k0)) - cuts.begin());
+      queues[x].push_back(WorkItem{t.seq, t.kvh, t.q_row0, p.k0 * BLOCK_N,
+                                   std::min(p.k1 * BLOCK_N, t.kv_len), part, t.rows, 0});
+    }
+  }
+}
 
 }  // namespace
 
@@ -49,26 +398,32 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
                              int32_t num_cus, int32_t num_xcds, const Tuning& tuning,
                              const int32_t* cu_rows, const int32_t* bt_rows) {
   ExtendPlan plan;
+  plan.part_rows = block_m;
   plan.seqs.resize(num_seqs);
-  int64_t cu = 0;
+  int64_t cu = 0, n_tiles = 0;
   for (int32_t b = 0; b < num_seqs; ++b) {
     plan.seqs[b] = SeqInfo{prefix_lens[b], suffix_lens[b],
                            cu_rows ? cu_rows[b] : static_cast<int32_t>(cu), bt_rows ? bt_rows[b] : b};
     cu += suffix_lens[b];
+    n_tiles += (int64_t(suffix_lens[b]) * gqa_group + block_m - 1) / block_m * num_kv_heads;
   }
 
-  // 1. query tiles, per sequence and kv head
+  // 1. query tiles, bundle by bundle (the tiles of one sequence and kv head)
   std::vector<Tile> tiles;
+  std::vector<Bundle> tile_bundles;
+  tiles.reserve(static_cast<size_t>(n_tiles));
   int64_t total_kt = 0;
   for (int32_t b = 0; b < num_seqs; ++b) {
     const int64_t rows = int64_t(suffix_lens[b]) * gqa_group;
-    for (int64_t r0 = 0; r0 < rows; r0 += block_m) {
-      const int32_t nr = static_cast<int32_t>(std::min<int64_t>(block_m, rows - r0));
-      const int64_t t_last = (r0 + nr - 1) / gqa_group;
-      const int32_t kv_len = static_cast<int32_t>(prefix_lens[b] + t_last + 1);
-      const int32_t n_kt = (kv_len + BLOCK_N - 1) / BLOCK_N;
-      for (int32_t h = 0; h < num_kv_heads; ++h) {
-        tiles.push_back(Tile{b, h, static_cast<int32_t>(r0), nr, kv_len, n_kt});
+    for (int32_t h = 0; rows > 0 && h < num_kv_heads; ++h) {
+      tile_bundles.push_back(Bundle{static_cast<int64_t>(tiles.size()), (rows + block_m - 1) / block_m, 0});
+      for (int64_t r0 = 0; r0 < rows; r0 += block_m) {
+        const int32_t nr = static_cast<int32_t>(std::min<int64_t>(block_m, rows - r0));
+        const int64_t t_last = (r0 + nr - 1) / gqa_group;
+        const int32_t kv_len = static_cast<int32_t>(prefix_lens[b] + t_last + 1);
+        const int32_t n_kt = (kv_len + BLOCK_N - 1) / BLOCK_N;
+        tiles.push_back(Tile{b, h, static_cast<int32_t>(r0), nr, kv_len, n_kt,
+                             std::min(n_kt, prefix_lens[b] / BLOCK_N)});
         total_kt += n_kt;
       }
     }
@@ -93,37 +448,22 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
     return std::max<int64_t>(1, std::min<int64_t>(n, n_kt / MIN_CHUNK_TILES));
   };
 
-  // 3. work items grouped into bundles by (sequence, kv head)
+  // 3. work items, bundle by bundle, a bundle's first chunks before its second ones
+  std::vector<WorkItem> items;
   std::vector<Bundle> bundles;
-  {
-    int32_t cur_seq = -1, cur_kvh = -1;
-    std::vector<std::vector<WorkItem>> chunk_major;  // [chunk][tile] inside a bundle
-    auto flush = [&]() {
-      if (chunk_major.empty()) return;
-      Bundle bd;
-      for (auto& v : chunk_major)
-        for (auto& it : v) {
-          bd.items.push_back(it);
-          bd.cost += (it.kv_end - it.kv_begin + BLOCK_N - 1) / BLOCK_N;
-        }
-      bundles.push_back(std::move(bd));
-      chunk_major.clear();
-    };
-    // tiles are ordered (seq, q tile, kvh); regroup them per (seq, kvh)
-    std::vector<size_t> order(tiles.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t c) {
-      if (tiles[a].seq != tiles[c].seq) return tiles[a].seq < tiles[c].seq;
-      return tiles[a].kvh < tiles[c].kvh;
-    });
-    for (size_t oi : order) {
-      const Tile& t = tiles[oi];
-      if (t.seq != cur_seq || t.kvh != cur_kvh) {
-        flush();
-        cur_seq = t.seq;
-        cur_kvh = t.kvh;
-      }
+  std::vector<int64_t> first;  // of the bundle's tiles: first key tile of each chunk, and the end
+  std::vector<std::pair<int64_t, int32_t>> chunk_at;  // of each tile: where its chunks start in `first`; part0
+  items.reserve(tiles.size());
+  bundles.reserve(tile_bundles.size());
+  for (const Bundle& tb : tile_bundles) {
+    Bundle bd{static_cast<int64_t>(items.size()), 0, 0};
+    first.clear();
+    chunk_at.clear();
+    int64_t most = 1;
+    for (int64_t ti = tb.first; ti < tb.first + tb.n; ++ti) {
+      const Tile& t = tiles[ti];
       const int64_t n_c = n_chunks(t.n_kt);
+      most = std::max(most, n_c);
       int32_t part0 = -1;
       if (n_c > 1) {
         part0 = static_cast<int32_t>(plan.n_parts);
@@ -131,36 +471,45 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
                                            static_cast<int32_t>(n_c), 0, 0});
         plan.n_parts += n_c;
       }
+      chunk_at.emplace_back(static_cast<int64_t>(first.size()), part0);
       // chunk boundaries: equal shares of the tile's cost, a key tile that
       // reaches past the cached prefix (masked, read from the new tokens)
       // costing suffix_weight / 100 of a prefix tile (forced chunk sizes:
-      // equal key counts)
-      const int64_t n_pre = std::min<int64_t>(t.n_kt, prefix_lens[t.seq] / BLOCK_N);
+      // equal key counts); every chunk at least one tile long
+      const int64_t n_pre = t.n_pre;
       const int64_t wgt = tuning.kv_chunk_tiles > 0 ? 100 : std::max(1, tuning.suffix_weight);
       const int64_t total_cost = n_pre * 100 + (t.n_kt - n_pre) * wgt;
-      // first key tile of each chunk, every chunk at least one tile long
-      std::vector<int64_t> first(static_cast<size_t>(n_c) + 1);
-      first[0] = 0;
-      first[n_c] = t.n_kt;
+      first.push_back(0);
       for (int64_t c = 1; c < n_c; ++c) {
         int64_t b = c * t.n_kt / n_c;
         if (wgt != 100) {
           const int64_t goal = c * total_cost / n_c;
           b = goal <= n_pre * 100 ? (goal + 99) / 100 : n_pre + (goal - n_pre * 100 + wgt - 1) / wgt;
         }
-        first[c] = std::min(std::max(b, first[c - 1] + 1), t.n_kt - (n_c - c));
+        first.push_back(std::min(std::max(b, first.back() + 1), t.n_kt - (n_c - c)));
       }
-      for (int64_t c = 0; c < n_c; ++c) {
-        const int64_t kt0 = first[c], kt1 = first[c + 1];
-        WorkItem it{t.seq, t.kvh, t.q_row0, static_cast<int32_t>(kt0 * BLOCK_N),
-                    static_cast<int32_t>(std::min<int64_t>(kt1 * BLOCK_N, t.kv_len)),
-                    n_c > 1 ? static_cast<int32_t>(part0 + c) : -1, t.rows, 0};
-        if (static_cast<int64_t>(chunk_major.size()) <= c) chunk_major.resize(c + 1);
-        chunk_major[c].push_back(it);
-      }
+      first.push_back(t.n_kt);
     }
-    flush();
+    for (int64_t c = 0; c < most; ++c)
+      for (int64_t i = 0; i < tb.n; ++i) {
+        const Tile& t = tiles[tb.first + i];
+        const int64_t at = chunk_at[i].first;
+        const int64_t end = i + 1 < tb.n ? chunk_at[i + 1].first : static_cast<int64_t>(first.size());
+        if (at + c + 1 >= end) continue;
+        const int64_t kt0 = first[at + c], kt1 = first[at + c + 1];
+        const int32_t part0 = chunk_at[i].second;
+        items.push_back(WorkItem{t.seq, t.kvh, t.q_row0, static_cast<int32_t>(kt0 * BLOCK_N),
+                                 static_cast<int32_t>(std::min<int64_t>(kt1 * BLOCK_N, t.kv_len)),
+                                 part0 >= 0 ? part0 + static_cast<int32_t>(c) : -1, t.rows, 0});
+        bd.cost += key_tiles(items.back());
+      }
+    bd.n = static_cast<int64_t>(items.size()) - bd.first;
+    bundles.push_back(bd);
   }
+  auto recount = [&](Bundle& bd) {
+    bd.cost = 0;
+    for (int64_t i = bd.first; i < bd.first + bd.n; ++i) bd.cost += key_tiles(items[i]);
+  };
 
   // 4. Bundles that fill whole rounds of the GPU (R items per XCD, one per
   // resident workgroup slot): dealt across every XCD a round at a time, so all
@@ -175,61 +524,65 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
   const int32_t X = std::max(1, num_xcds);
   const int64_t R = std::max<int64_t>(1, int64_t(std::max(1, wgs_per_cu)) * num_cus / X);
   std::vector<std::vector<WorkItem>> queues(X);
+  bool dealt = false;
   if (tuning.deal_rounds != 0) {
     int64_t round = 0;
     for (auto& bd : bundles) {
-      const int64_t n_rounds = static_cast<int64_t>(bd.items.size()) / (R * X);
+      const int64_t n_rounds = bd.n / (R * X);
       for (int64_t r = 0; r < n_rounds; ++r, ++round)
         for (int32_t x = 0; x < X; ++x) {
           // XCD x takes block (x + round) % X of the round's X blocks of R
           // items: blocks later in a bundle hold longer tiles (more keys), and
           // the rotation gives every XCD each position in turn
-          const auto b0 = bd.items.begin() + (r * X + (x + round) % X) * R;
+          const auto b0 = items.begin() + bd.first + (r * X + (x + round) % X) * R;
           if (round & 1) queues[x].insert(queues[x].end(), std::make_reverse_iterator(b0 + R),
                                           std::make_reverse_iterator(b0));
           else queues[x].insert(queues[x].end(), b0, b0 + R);
         }
       if (n_rounds > 0) {
-        bd.items.erase(bd.items.begin(), bd.items.begin() + n_rounds * R * X);
-        bd.cost = 0;
-        for (auto& w : bd.items) bd.cost += (w.kv_end - w.kv_begin + BLOCK_N - 1) / BLOCK_N;
+        dealt = true;
+        bd.first += n_rounds * R * X;
+        bd.n -= n_rounds * R * X;
+        recount(bd);
       }
     }
-    bundles.erase(std::remove_if(bundles.begin(), bundles.end(),
-                                 [](const Bundle& b) { return b.items.empty(); }),
+    bundles.erase(std::remove_if(bundles.begin(), bundles.end(), [](const Bundle& b) { return b.n == 0; }),
                   bundles.end());
   }
 
   // 5. enough bundles to occupy every XCD: halve the largest while possible
   while (static_cast<int32_t>(bundles.size()) < 2 * X) {
     auto it = std::max_element(bundles.begin(), bundles.end(),
-                               [](const Bundle& a, const Bundle& c) { return a.items.size() < c.items.size(); });
-    if (it == bundles.end() || it->items.size() < 2) break;
-    Bundle hi;
-    const size_t half = it->items.size() / 2;
-    hi.items.assign(it->items.begin() + half, it->items.end());
-    it->items.resize(half);
-    it->cost = hi.cost = 0;
-    for (auto& w : it->items) it->cost += (w.kv_end - w.kv_begin + BLOCK_N - 1) / BLOCK_N;
-    for (auto& w : hi.items) hi.cost += (w.kv_end - w.kv_begin + BLOCK_N - 1) / BLOCK_N;
-    bundles.push_back(std::move(hi));
+                               [](const Bundle& a, const Bundle& c) { return a.n < c.n; });
+    if (it == bundles.end() || it->n < 2) break;
+    const int64_t half = it->n / 2;
+    Bundle hi{it->first + half, it->n - half, 0};
+    it->n = half;
+    recount(*it);
+    recount(hi);
+    bundles.push_back(hi);
   }
 
   // 6. LPT assignment of the other bundles to XCD queues (after the dealt
-  // rounds, which every queue holds the same number of), then interleave
+  // rounds, which every queue holds the same number of), levelled where the
+  // workgroups would finish far apart, then interleave
   std::stable_sort(bundles.begin(), bundles.end(),
                    [](const Bundle& a, const Bundle& c) { return a.cost > c.cost; });
   std::vector<int64_t> load(X, 0);
   for (auto& bd : bundles) {
     const int32_t x = static_cast<int32_t>(std::min_element(load.begin(), load.end()) - load.begin());
     load[x] += bd.cost;
-    queues[x].insert(queues[x].end(), bd.items.begin(), bd.items.end());
+    queues[x].insert(queues[x].end(), items.begin() + bd.first, items.begin() + bd.first + bd.n);
   }
+  plan.whole_meta_bytes = plan_meta_bytes(plan.seqs.size(), launch_count(queues), plan.groups.size());
+  if (tuning.kv_chunk_tiles == 0 && tuning.target_wgs == 0 && !dealt)
+    level_plan(plan, tiles, tile_bundles, std::max(1, tuning.suffix_weight), R, head_dim, queues);
   size_t max_len = 0;
   for (auto& qv : queues) max_len = std::max(max_len, qv.size());
   const WorkItem idle{-1, 0, 0, 0, 0, -1, 0, 0};
   int32_t used_queues = 0;
   for (auto& qv : queues) used_queues += qv.empty() ? 0 : 1;
+  plan.items.reserve(max_len * static_cast<size_t>(X));
   for (size_t i = 0; i < max_len; ++i)
     for (int32_t x = 0; x < X; ++x) {
       if (i < queues[x].size()) plan.items.push_back(queues[x][i]);
@@ -239,7 +592,6 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
   while (!plan.items.empty() && plan.items.back().seq < 0) plan.items.pop_back();
 
   // 7. workspace layout
-  plan.part_rows = block_m;
   layout_workspace(plan, head_dim);
   return plan;
 }
@@ -319,6 +671,7 @@ ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32
   });
   plan.items.insert(plan.items.end(), tails.begin(), tails.end());
   layout_workspace(plan, head_dim);
+  plan.whole_meta_bytes = plan.meta_bytes;
 
   // the compact form: one record per sequence, the order of the last chunks
   plan.compact = true;

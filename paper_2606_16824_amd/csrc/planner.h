@@ -11,6 +11,15 @@
 
 namespace cw {
 
+// Plans of at most kMaxLevelTiles query tiles may be levelled (tiles cut into key
+// ranges so that all workgroups finish together; longer work lists are level
+// enough whole), with at most kLevelPartBytes of partial slots (so that the plan
+// fits the library's static scratch array) and a meta of at most kLevelMetaBytes
+// more than the plan would have had otherwise.
+constexpr int64_t kMaxLevelTiles = 4096;
+constexpr int64_t kLevelPartBytes = int64_t(48) << 20;
+constexpr size_t kLevelMetaBytes = size_t(64) << 10;
+
 struct Tuning {
   int32_t kv_chunk_tiles = 0;  // 0 = automatic
   int32_t target_wgs = 0;      // 0 = automatic
@@ -30,6 +39,9 @@ struct ExtendPlan {
   // Workspace layout (byte offsets, 256-byte aligned).
   size_t off_seqs = 0, off_items = 0, off_groups = 0, off_part_o = 0, off_part_ml = 0;
   size_t meta_bytes = 0;  // seqs + items + groups: the part uploaded per call
+  // extend plans: meta_bytes of the plan before levelling.  The limits on a call's
+  // plan are limits on this, so that levelling refuses nothing.
+  size_t whole_meta_bytes = 0;
   size_t total_bytes = 0;
   int32_t part_rows = 0;  // rows per partial slot
   // decode plans: the same items and groups in compact form (see plan_expand.h)

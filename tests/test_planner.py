@@ -124,3 +124,53 @@ def test_forced_chunking():
         assert np.all(real[:, 4] - real[:, 3] <= 3 * BN)
     finally:
         cwlib.set_tuning(0, 0)
+
+
+RATE = (72, 72, 72, 72, 80, 89, 95, 100)  # cost of a key tile by 32-row waves in use
+
+
+def finish_times(items, lp):
+    """Finishing time of every slot (8 XCDs x 32 CUs, one workgroup each) when the
+    items go to their XCD's first free slot, in the planner's cost units."""
+    t = np.zeros((8, 32))
+    for i, (seq, _, _, kb, ke, _, rows, _) in enumerate(items):
+        if seq < 0:
+            continue
+        k0, k1 = kb // BN, -(-ke // BN)
+        pre = max(0, min(k1, lp[seq] // BN) - k0)
+        x = t[i % 8]
+        x[x.argmin()] += 300 + (pre * 100 + (k1 - k0 - pre) * 125) * RATE[(rows - 1) // 32] / 100
+    return t
+
+
+@pytest.mark.parametrize("lp,ls,hkv,g,cut", [
+    # one tile more than fits a round; short replies on long prefixes; turns of all
+    # lengths (whole tiles in another order level them); an odd number of heads
+    # (bundles spread over XCDs); wide heads; no cached prefix
+    ([20000] * 33, [64] * 33, 8, 4, True),
+    ([19000, 31000, 5000, 12000, 27000, 9000, 30000, 8000, 22000, 16000],
+     [598, 59, 14, 66, 154, 15, 54, 30, 542, 402], 8, 4, True),
+    ([18504, 43579, 48305, 23677, 64755, 14911, 24185], [3506, 1864, 3197, 2380, 383, 1686, 2631], 8, 4, False),
+    ([70000, 500], [2500, 1], 3, 8, True),
+    ([40000] * 5, [700] * 5, 1, 16, True),
+    ([0] * 4, [4071, 4153, 3780, 3373], 8, 4, False),
+])
+def test_levelled_plan(lp, ls, hkv, g, cut):
+    """Calls that a plan of whole tiles leaves uneven: every key is still covered
+    once, cut pieces hold at least four key tiles, all slots finish within 6% of the
+    mean, and the meta stays within 64 KiB of the whole-tile plan's."""
+    items = check_plan(np.array(lp), np.array(ls), hkv, g)
+    real = items[items[:, 0] >= 0]
+    parts = real[real[:, 5] >= 0]
+    assert (len(parts) > 0) == cut
+    assert np.all(-(-(parts[:, 4] - parts[:, 3]) // BN) >= 4)
+    t = finish_times(items, lp)
+    assert t.max() <= 1.06 * t.mean()
+    cwlib.set_tuning(1, 256)  # a target in the place of the automatic one: whole tiles, or equal chunks
+    try:
+        whole = check_plan(np.array(lp), np.array(ls), hkv, g)
+    finally:
+        cwlib.set_tuning(1, 0)
+    assert finish_times(whole, lp).max() > 1.04 * t.max()
+    n_groups = len(np.unique(parts[:, :3], axis=0))
+    assert len(items) * 32 + n_groups * 32 <= len(whole) * 32 + (64 << 10)
