@@ -155,8 +155,9 @@ hipError_t launch_decode(const ExtendParams& p, int head_dim, int page_size, boo
                          hipStream_t stream, const ArgPlan* ap = nullptr);
 int decode_keys_per_tile(int head_dim, bool fp8);
 int decode_waves_per_cu(bool fp8);  // resident decode waves per CU (LDS-bound)
+// (the argument plan is the sequences alone, at its byte 0)
 hipError_t launch_write_pages(const WriteParams& p, int head_dim, int page_size, bool fp8,
-                              hipStream_t stream);
+                              hipStream_t stream, const ArgPlan* ap = nullptr);
 hipError_t launch_swap(const SwapParams& p, hipStream_t stream);
 // Copies `bytes` from device-visible pinned host memory to device memory on
 // `stream` with a kernel (the plan upload).  With `done` (device address of
