@@ -62,7 +62,7 @@ def _lens(x) -> np.ndarray:
 
 
 def _ptr(a: Optional[np.ndarray]):
-    return None if a is None or a.size == 0 else a.ctypes.data
+    return None if a is None or a.size == 0 else a.__array_interface__["data"][0]
 
 
 def _dptr(t: Optional[torch.Tensor]):
@@ -107,10 +107,55 @@ def _check_pools(k_pool, v_pool, k_scale, v_scale):
     return num_pages, hkv, page, d
 
 
+def _quick_check(q, k_new, v_new, k_pool, v_pool, block_table, num_seqs, total, g, k_scale, v_scale,
+                 out, lse):
+    """The pool dimensions if every check of _check_call passes, else None (which of
+    them failed is then found out, and raised, one check at a time).  A small call's
+    own work takes 10 us on the GPU, and checking it argument by argument took 5."""
+    try:
+        pool_shape = k_pool.shape
+        num_pages, hkv, page, d = pool_shape
+        dt = k_pool.dtype
+        dev = k_pool.get_device()
+        if dev < 0 or v_pool.dtype is not dt or v_pool.shape != pool_shape or v_pool.get_device() != dev:
+            return None
+        if dt is torch.bfloat16:
+            if k_scale is not None or v_scale is not None:
+                return None
+        elif dt in _FP8:
+            pair = (num_pages, hkv)
+            if not (k_scale.dtype is torch.float32 and k_scale.shape == pair and k_scale.get_device() == dev
+                    and v_scale.dtype is torch.float32 and v_scale.shape == pair and v_scale.get_device() == dev):
+                return None
+        else:
+            return None
+        if type(g) is not int or g < 1:
+            return None
+        rows = (total, hkv * g, d)
+        new = (total, hkv, d)
+        if not (block_table.dtype is torch.int32 and block_table.dim() == 2 and block_table.shape[0] >= num_seqs
+                and block_table.get_device() == dev
+                and k_new.dtype is torch.bfloat16 and k_new.shape == new and k_new.get_device() == dev
+                and v_new.dtype is torch.bfloat16 and v_new.shape == new and v_new.get_device() == dev):
+            return None
+        for t in (q, out):
+            if t is not None and not (t.dtype is torch.bfloat16 and t.shape == rows and t.get_device() == dev):
+                return None
+        if lse is not None and not (lse.dtype is torch.float32 and lse.shape == rows[:2] and lse.get_device() == dev):
+            return None
+        return num_pages, hkv, page, d
+    except (AttributeError, TypeError, ValueError):
+        return None
+
+
 def _check_call(q, k_new, v_new, k_pool, v_pool, block_table, num_seqs, total, gqa_group,
                 k_scale=None, v_scale=None, out=None, lse=None):
     """dtype and shape of every tensor of an attention call against its lengths
     (`total` packed rows, `num_seqs` sequences); returns the pool dimensions."""
+    dims = _quick_check(q, k_new, v_new, k_pool, v_pool, block_table, num_seqs, total, gqa_group,
+                        k_scale, v_scale, out, lse)
+    if dims is not None:
+        return dims
     num_pages, hkv, page, d = _check_pools(k_pool, v_pool, k_scale, v_scale)
     if not isinstance(block_table, torch.Tensor) or block_table.dim() != 2 \
             or block_table.dtype != torch.int32:
@@ -158,7 +203,12 @@ def arg_plan_calls() -> int:
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current HIP stream on the current device, as an integer."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _total(ls: np.ndarray) -> int:
+    return sum(ls.tolist()) if ls.size <= 64 else int(ls.sum())
 
 
 def _kv_dtype(pool: torch.Tensor) -> int:
@@ -242,7 +292,7 @@ def kv_write_pages(k_new, v_new, k_pool, v_pool, block_table, prefix_lens, suffi
                    k_scale=None, v_scale=None, workspace=None):
     lp, ls = _lens_pair(prefix_lens, suffix_lens)
     num_pages, hkv, page, d = _check_call(None, k_new, v_new, k_pool, v_pool, block_table, len(lp),
-                                          int(ls.sum()), 1, k_scale, v_scale)
+                                          _total(ls), 1, k_scale, v_scale)
     ws = _workspace(write_pages_workspace_bytes(len(lp)), k_pool.device, workspace)
     _check(library().cw_kv_write_pages(
         _dptr(k_new), _dptr(v_new), _dptr(k_pool), _dptr(v_pool), _dptr(k_scale), _dptr(v_scale),
@@ -255,7 +305,7 @@ def extend_attention(q, k_new, v_new, k_pool, v_pool, block_table, prefix_lens, 
                      workspace=None):
     lp, ls = _lens_pair(prefix_lens, suffix_lens)
     num_pages, hkv, page, d = _check_call(q, k_new, v_new, k_pool, v_pool, block_table, len(lp),
-                                          int(ls.sum()), gqa_group, k_scale, v_scale, out, lse)
+                                          _total(ls), gqa_group, k_scale, v_scale, out, lse)
     if out is None:
         out = torch.empty_like(q)
     if workspace is None:
@@ -277,7 +327,7 @@ def extend_attention_noalloc(q, k_new, v_new, k_pool, v_pool, block_table, prefi
     `out` given, the call allocates nothing."""
     lp, ls = _lens_pair(prefix_lens, suffix_lens)
     num_pages, hkv, page, d = _check_call(q, k_new, v_new, k_pool, v_pool, block_table, len(lp),
-                                          int(ls.sum()), gqa_group, k_scale, v_scale, out, lse)
+                                          _total(ls), gqa_group, k_scale, v_scale, out, lse)
     if out is None:
         out = torch.empty_like(q)
     _check(library().cw_extend_attention_noalloc(
@@ -294,7 +344,7 @@ def write_extend_attention(q, k_new, v_new, k_pool, v_pool, block_table, prefix_
     """kv_write_pages + extend_attention in one launch (the pools are written)."""
     lp, ls = _lens_pair(prefix_lens, suffix_lens)
     num_pages, hkv, page, d = _check_call(q, k_new, v_new, k_pool, v_pool, block_table, len(lp),
-                                          int(ls.sum()), gqa_group, k_scale, v_scale, out, lse)
+                                          _total(ls), gqa_group, k_scale, v_scale, out, lse)
     if out is None:
         out = torch.empty_like(q)
     if workspace is None:
@@ -321,7 +371,7 @@ def step_attention(q, k_new, v_new, k_pool, v_pool, block_table, prefix_lens, su
     """One serving step: page write + attention, decodes on the decode kernel."""
     lp, ls = _lens_pair(prefix_lens, suffix_lens)
     num_pages, hkv, page, d = _check_call(q, k_new, v_new, k_pool, v_pool, block_table, len(lp),
-                                          int(ls.sum()), gqa_group, k_scale, v_scale, out, lse)
+                                          _total(ls), gqa_group, k_scale, v_scale, out, lse)
     if out is None:
         out = torch.empty_like(q)
     if workspace is None:

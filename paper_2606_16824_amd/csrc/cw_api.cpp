@@ -10,6 +10,7 @@
 #include <cstring>
 #include <exception>
 #include <initializer_list>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -514,6 +515,44 @@ int64_t sum_suffix(const int32_t* ls, int32_t num_seqs) {
   return t;
 }
 
+// The last plan this thread made of each kind.  The layers of a model call with the
+// same lengths one after the other, and a workspace query asks for the plan of the
+// call that follows it: planning 300 to 2000 work items takes 25-130 us of host
+// time, comparing the lengths and options that a plan is made from (all of them)
+// well under one.  A plan holds no pointer of a call.  Plans above
+// kMaxKeptPlanBytes are not kept, and a thread's plans go with the thread.
+constexpr size_t kMaxKeptPlanBytes = size_t(1) << 20;
+template <class Plan>
+class LastPlan {
+ public:
+  template <class Make, class Bytes>
+  std::shared_ptr<const Plan> get(const int32_t* lp, const int32_t* ls, int32_t num_seqs,
+                                  std::initializer_list<int32_t> options, Make&& make, Bytes&& bytes) {
+    int32_t cus = 256, xcds = 8;
+    device_shape(&cus, &xcds);
+    const Tuning t = current_tuning();
+    key_.clear();
+    key_.insert(key_.end(), options);
+    key_.insert(key_.end(), {num_seqs, cus, xcds, t.kv_chunk_tiles, t.target_wgs, t.deal_rounds, t.suffix_weight});
+    key_.insert(key_.end(), lp, lp + num_seqs);
+    if (ls != nullptr) key_.insert(key_.end(), ls, ls + num_seqs);
+    if (plan_ && key_ == kept_) return plan_;
+    std::shared_ptr<const Plan> p = std::make_shared<const Plan>(make());
+    if (bytes(*p) + key_.size() * sizeof(int32_t) <= kMaxKeptPlanBytes) {
+      plan_ = p;
+      kept_.swap(key_);
+    }
+    return p;
+  }
+
+ private:
+  std::vector<int32_t> key_, kept_;
+  std::shared_ptr<const Plan> plan_;
+};
+size_t kept_bytes(const ExtendPlan& p) {
+  return (p.items.size() + p.groups.size()) * 32 + p.seqs.size() * 16 + p.recs.size() * sizeof(DecodeRec);
+}
+
 // Both pool dtypes run the LDS-staged kernel with the same row block
 // (LDS_BLOCK_M rows per work item, one workgroup per CU), so the extend plan
 // does not depend on the pool dtype.
@@ -538,6 +577,23 @@ ExtendPlan make_decode_plan(const int32_t* lp, int32_t num_seqs, int32_t num_kv_
   return build_decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size,
                            decode_keys_per_tile(head_dim, fp8), decode_waves_per_cu(fp8), cus,
                            current_tuning(), cu_rows, bt_rows);
+}
+
+std::shared_ptr<const ExtendPlan> extend_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs,
+                                              int32_t num_kv_heads, int32_t gqa_group, int32_t head_dim) {
+  thread_local LastPlan<ExtendPlan> last;
+  return last.get(lp, ls, num_seqs, {num_kv_heads, gqa_group, head_dim},
+                  [&]() { return make_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim); }, kept_bytes);
+}
+std::shared_ptr<const ExtendPlan> decode_plan(const int32_t* lp, int32_t num_seqs, int32_t num_kv_heads,
+                                              int32_t gqa_group, int32_t head_dim, int32_t page_size,
+                                              cw_kv_dtype_t kv_dtype) {
+  thread_local LastPlan<ExtendPlan> last;
+  return last.get(lp, nullptr, num_seqs, {num_kv_heads, gqa_group, head_dim, page_size, int32_t(kv_dtype)},
+                  [&]() {
+                    return make_decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+                  },
+                  kept_bytes);
 }
 
 // A step of a serving engine: the sequences with one new token go to the decode
@@ -588,6 +644,19 @@ StepPlan make_step_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs, 
   return sp;
 }
 
+std::shared_ptr<const StepPlan> step_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs,
+                                          int32_t num_kv_heads, int32_t gqa_group, int32_t head_dim,
+                                          int32_t page_size, cw_kv_dtype_t kv_dtype) {
+  thread_local LastPlan<StepPlan> last;
+  return last.get(lp, ls, num_seqs, {num_kv_heads, gqa_group, head_dim, page_size, int32_t(kv_dtype)},
+                  [&]() {
+                    return make_step_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+                  },
+                  [](const StepPlan& p) {
+                    return kept_bytes(p.ext_plan) + kept_bytes(p.dec_plan) + p.seqs.size() * 24;
+                  });
+}
+
 // Kernel arguments of a plan whose meta is read at `meta` and whose partials
 // sit at ws + part.
 ExtendParams plan_params(const ExtendPlan& plan, const uint8_t* meta, uint8_t* ws, size_t part) {
@@ -635,8 +704,10 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
   if (lse && (reinterpret_cast<uintptr_t>(lse) & 3u)) return fail(CW_ERR_ALIGN, "lse not 4-byte aligned");
   if ((reinterpret_cast<uintptr_t>(block_table) & 3u)) return fail(CW_ERR_ALIGN, "block_table not 4-byte aligned");
 
-  ExtendPlan plan = decode ? make_decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype)
-                           : make_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim);
+  const std::shared_ptr<const ExtendPlan> kept =
+      decode ? decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype)
+             : extend_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim);
+  const ExtendPlan& plan = *kept;
   if (no_alloc && plan.total_bytes > workspace_bytes)
     return fail(CW_ERR_WORKSPACE, "the call needs %zu bytes of scratch; the static scratch array holds %zu",
                 plan.total_bytes, workspace_bytes);
@@ -714,9 +785,7 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
     if (e != hipSuccess) return hip_fail(e, "extend kernel launch");
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     if (p.n_groups > 0) {
-      int max_parts = 0;
-      for (const CombineGroup& g : plan.groups) max_parts = std::max(max_parts, g.n_parts);
-      e = launch_combine(p, head_dim, max_parts, stream, ap);
+      e = launch_combine(p, head_dim, plan.max_parts, stream, ap);
       if (e != hipSuccess) return hip_fail(e, "combine kernel launch");
     }
     return CW_OK;
@@ -829,7 +898,9 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
   if (lse && (reinterpret_cast<uintptr_t>(lse) & 3u)) return fail(CW_ERR_ALIGN, "lse not 4-byte aligned");
   if ((reinterpret_cast<uintptr_t>(block_table) & 3u)) return fail(CW_ERR_ALIGN, "block_table not 4-byte aligned");
 
-  const StepPlan sp = make_step_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+  const std::shared_ptr<const StepPlan> kept =
+      step_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+  const StepPlan& sp = *kept;
   if (workspace == nullptr || workspace_bytes < sp.total_bytes)
     return fail(CW_ERR_WORKSPACE, "workspace of %zu bytes, %zu needed", workspace_bytes, sp.total_bytes);
   s = check_attention_alias(q, k_new, v_new, k_pool, v_pool, k_scale, v_scale, block_table,
@@ -902,9 +973,7 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
       if (sp.ext.empty() && ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess)
         return hip_fail(e, "hipEventRecord");
       if (pd.n_groups > 0) {
-        int max_parts = 0;
-        for (const CombineGroup& g : sp.dec_plan.groups) max_parts = std::max(max_parts, g.n_parts);
-        if ((e = launch_combine(pd, head_dim, max_parts, stream, ap)) != hipSuccess)
+        if ((e = launch_combine(pd, head_dim, sp.dec_plan.max_parts, stream, ap)) != hipSuccess)
           return hip_fail(e, "combine kernel launch");
       }
     }
@@ -927,9 +996,7 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
         return hip_fail(e, "extend kernel launch");
       if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return hip_fail(e, "hipEventRecord");
       if (pe.n_groups > 0) {
-        int max_parts = 0;
-        for (const CombineGroup& g : sp.ext_plan.groups) max_parts = std::max(max_parts, g.n_parts);
-        if ((e = launch_combine(pe, head_dim, max_parts, stream, ap)) != hipSuccess)
+        if ((e = launch_combine(pe, head_dim, sp.ext_plan.max_parts, stream, ap)) != hipSuccess)
           return hip_fail(e, "combine kernel launch");
       }
     }
@@ -1124,7 +1191,7 @@ size_t cw_extend_workspace_bytes(const int32_t* prefix_lens_h, const int32_t* su
                    head_dim, false) != CW_OK)
       return 0;
     if (num_seqs == 0) return 256;
-    return make_plan(prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim).total_bytes;
+    return extend_plan(prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim)->total_bytes;
   });
 }
 
@@ -1172,9 +1239,8 @@ size_t cw_step_workspace_bytes(const int32_t* prefix_lens_h, const int32_t* suff
                    head_dim, false) != CW_OK)
       return 0;
     if (num_seqs == 0) return 256;
-    return make_step_plan(prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim,
-                          page_size, kv_dtype)
-        .total_bytes;
+    return step_plan(prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype)
+        ->total_bytes;
   });
 }
 
@@ -1206,8 +1272,8 @@ size_t cw_decode_workspace_bytes(const int32_t* prefix_lens_h, int32_t num_seqs,
                    head_dim, false) != CW_OK)
       return 0;
     if (num_seqs == 0) return 256;
-    return make_decode_plan(prefix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype)
-        .total_bytes;
+    return decode_plan(prefix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype)
+        ->total_bytes;
   });
 }
 

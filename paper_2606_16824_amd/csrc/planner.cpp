@@ -602,6 +602,7 @@ void layout_workspace(ExtendPlan& plan, int32_t head_dim) {
   plan.off_items = align256(plan.off_seqs + plan.seqs.size() * sizeof(SeqInfo));
   plan.off_groups = align256(plan.off_items + plan.items.size() * sizeof(WorkItem));
   plan.meta_bytes = align256(plan.off_groups + plan.groups.size() * sizeof(CombineGroup));
+  for (const CombineGroup& g : plan.groups) plan.max_parts = std::max(plan.max_parts, g.n_parts);
   plan.off_part_o = plan.meta_bytes;
   // the partial O is stored in bf16 (2 bytes), the running max and sum in fp32
   plan.off_part_ml = align256(plan.off_part_o + size_t(plan.n_parts) * plan.part_rows * head_dim * 2);

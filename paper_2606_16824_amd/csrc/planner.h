@@ -36,6 +36,7 @@ struct ExtendPlan {
   std::vector<WorkItem> items;  // launch order
   std::vector<CombineGroup> groups;
   int64_t n_parts = 0;
+  int32_t max_parts = 0;  // partial slots of the group that has most
   // Workspace layout (byte offsets, 256-byte aligned).
   size_t off_seqs = 0, off_items = 0, off_groups = 0, off_part_o = 0, off_part_ml = 0;
   size_t meta_bytes = 0;  // seqs + items + groups: the part uploaded per call

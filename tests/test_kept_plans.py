@@ -1,0 +1,61 @@
+"""The plan a thread keeps from its last call is used only for the very same lengths
+and options: workspace sizes asked for in a mixed order on one thread equal those
+asked for on threads of their own, which keep nothing (runs on the CPU)."""
+import threading
+
+import numpy as np
+
+import paper_2606_16824_amd as cwlib
+
+
+def _sizes(q):
+    kind, lp, ls, hkv, g, d, p, dt, tune = q
+    for key, value in tune.items():
+        cwlib.set_tuning(key, value)
+    try:
+        if kind == "extend":
+            return cwlib.extend_workspace_bytes(lp, ls, hkv, g, d, p)
+        if kind == "decode":
+            return cwlib.decode_workspace_bytes(lp, hkv, g, d, p, dt)
+        return cwlib.step_workspace_bytes(lp, ls, hkv, g, d, p, dt)
+    finally:
+        cwlib.set_tuning(0, 0)
+        cwlib.set_tuning(1, 0)
+        cwlib.set_tuning(3, 1)
+        cwlib.set_tuning(5, 125)
+
+
+def test_kept_plan_only_for_the_same_call():
+    base = ("step", [5000, 70, 0, 16000], [1, 64, 300, 1], 8, 4, 128, 16, "bf16", {})
+    queries = [base]
+    for i, other in ((1, [5000, 70, 0, 16001]), (2, [1, 64, 301, 1]), (3, 4), (4, 8), (5, 64), (6, 64), (7, "fp8"),
+                     (8, {0: 3}), (8, {1: 64}), (8, {5: 300}), (8, {3: 0}), (0, "extend"), (0, "decode")):
+        q = list(base)
+        q[i] = other
+        queries.append(tuple(q))
+    # one sequence fewer or more, and two lists that only differ in where they are cut
+    queries += [("extend", [100, 200], [50, 60], 2, 4, 64, 16, "bf16", {}), ("extend", [100], [200], 2, 4, 64, 16, "bf16", {}),
+                ("decode", [100, 200, 50, 60], None, 2, 4, 64, 16, "bf16", {})]
+    fresh = {}
+
+    def ask(i):
+        fresh[i] = _sizes(queries[i])
+
+    for i in range(len(queries)):
+        t = threading.Thread(target=ask, args=(i,))
+        t.start()
+        t.join()
+    assert len(set(fresh.values())) > 5
+    rng = np.random.default_rng(0)
+    for i in list(range(len(queries))) * 2 + rng.integers(0, len(queries), 200).tolist():
+        assert _sizes(queries[i]) == fresh[i], queries[i]
+
+
+def test_lengths_changed_in_place():
+    """The caller's array may be reused with other lengths: the plan follows its values."""
+    lp, ls = np.array([4000, 9000], np.int32), np.array([700, 1], np.int32)
+    first = cwlib.step_workspace_bytes(lp, ls, 8, 4, 128, 16, "bf16")
+    lp[0] = 60000
+    other = cwlib.step_workspace_bytes(lp, ls, 8, 4, 128, 16, "bf16")
+    lp[0] = 4000
+    assert cwlib.step_workspace_bytes(lp, ls, 8, 4, 128, 16, "bf16") == first != other
