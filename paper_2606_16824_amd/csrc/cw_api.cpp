@@ -64,7 +64,7 @@ Tuning current_tuning() {
 // one (64 rows per wave, bf16 pools only) is asked for.  Both own LDS_BLOCK_M
 // rows per work item, so they share the plan.
 hipError_t launch_extend(const ExtendParams& p, int head_dim, int page_size, bool fp8,
-                         hipStream_t stream, const ArgPlan* ap) {
+                         hipStream_t stream, const ArgPlanBuf* ap) {
   if (!fp8 && current_tuning().extend_kernel == 2) return launch_extend_w64(p, head_dim, page_size, stream, ap);
   return launch_extend_lds(p, head_dim, page_size, fp8, stream, ap);
 }
@@ -301,15 +301,17 @@ cw_status_t stage_and_launch(size_t bytes, size_t whole_bytes, void* dst, hipStr
     // its ExpandDesc behind the records, else as it is
     if (compact != nullptr && compact->plan != nullptr) {
       if (compact_arg_fits(*compact)) {
-        ArgPlan ap;
-        fill_compact(*compact, ap.bytes, fill_head);
-        std::memcpy(ap.bytes + compact->bytes, &compact->desc, sizeof(ExpandDesc));
+        ArgPlanBuf ap;
+        fill_compact(*compact, ap.plan.bytes, fill_head);
+        std::memcpy(ap.plan.bytes + compact->bytes, &compact->desc, sizeof(ExpandDesc));
+        ap.used = compact->bytes + sizeof(ExpandDesc);
         g_arg_plan_calls.fetch_add(1);
         return launch(nullptr, &ap);
       }
     } else if (bytes <= kArgPlanBytes) {
-      ArgPlan ap;
-      fill(ap.bytes);
+      ArgPlanBuf ap;
+      fill(ap.plan.bytes);
+      ap.used = bytes;
       g_arg_plan_calls.fetch_add(1);
       return launch(nullptr, &ap);
     }
@@ -392,7 +394,7 @@ cw_status_t stage_and_launch(size_t bytes, size_t whole_bytes, void* dst, hipStr
 
 template <class Fill>
 cw_status_t upload_fill(size_t bytes, void* dst, hipStream_t stream, Fill&& fill) {
-  return stage_and_launch(bytes, bytes, dst, stream, fill, [](const uint8_t*, const ArgPlan*) { return CW_OK; },
+  return stage_and_launch(bytes, bytes, dst, stream, fill, [](const uint8_t*, const ArgPlanBuf*) { return CW_OK; },
                           false, false, nullptr, fill);
 }
 
@@ -762,7 +764,7 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
   const bool fp8 = kv_dtype == CW_KV_FP8_E4M3FN;
   CompactUpload cu;
   const bool compact = decode && compact_upload(plan, 0, &cu);
-  auto launch = [&](const uint8_t* meta, const ArgPlan* ap) -> cw_status_t {
+  auto launch = [&](const uint8_t* meta, const ArgPlanBuf* ap) -> cw_status_t {
     if (ap != nullptr) {  // the plan is in the kernel arguments (decodes: in compact form)
       p.seqs = nullptr;
       p.items = nullptr;
@@ -947,7 +949,7 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
   const bool fp8 = kv_dtype == CW_KV_FP8_E4M3FN;
   CompactUpload cu;
   const bool compact = !sp.dec.empty() && compact_upload(sp.dec_plan, sp.off_dec_meta, &cu);
-  auto launch = [&](const uint8_t* meta, const ArgPlan* ap) -> cw_status_t {
+  auto launch = [&](const uint8_t* meta, const ArgPlanBuf* ap) -> cw_status_t {
     // with an argument plan (steps of extends only, or of decodes only with the
     // decode plan in compact form) the step's sequences sit at its byte 0, the
     // extend meta at off_ext_meta and the decode meta at off_dec_meta
@@ -1173,7 +1175,7 @@ cw_status_t cw_kv_write_pages(const void* k_new, const void* v_new, void* k_pool
     const size_t bytes = seqs.size() * sizeof(SeqInfo);
     const bool in_args = arg_plans() && capture == hipStreamCaptureStatusNone && bytes <= kArgPlanBytes;
     auto fill = [&](uint8_t* h) { std::memcpy(h, seqs.data(), bytes); };
-    auto launch = [&](const uint8_t* meta, const ArgPlan* ap) -> cw_status_t {
+    auto launch = [&](const uint8_t* meta, const ArgPlanBuf* ap) -> cw_status_t {
       p.seqs = reinterpret_cast<const SeqInfo*>(meta);
       const hipError_t e = launch_write_pages(p, head_dim, page_size, kv_dtype == CW_KV_FP8_E4M3FN, stream, ap);
       return e == hipSuccess ? CW_OK : hip_fail(e, "write_pages kernel launch");

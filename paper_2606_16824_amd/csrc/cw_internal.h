@@ -76,15 +76,33 @@ constexpr size_t kArgPlanBytes = 16384;
 struct ArgPlan {
   uint8_t bytes[kArgPlanBytes];
 };
+// Most plans of small calls fit a quarter of that, and a launch takes longer the
+// more argument bytes it carries (a 64-lane kernel launched back to back: 2.6 us each
+// with 2 KB, 3.0 with 4, 4.2 with 16), so there is a second size.
+constexpr size_t kArgSmallBytes = 4096;
+struct ArgPlanSmall {
+  uint8_t bytes[kArgSmallBytes];
+};
 struct NoArgPlan {
   uint8_t unused;
 };
-template <bool AP>
-using PlanArg = typename std::conditional<AP, ArgPlan, NoArgPlan>::type;
+// What a kernel's AP parameter says about its plan.
+constexpr int kPlanInMemory = 0, kPlanInArgs = 1, kPlanInSmallArgs = 2;
+template <int AP>
+using PlanArg = typename std::conditional<AP == kPlanInArgs, ArgPlan,
+                                          typename std::conditional<AP == kPlanInSmallArgs, ArgPlanSmall,
+                                                                    NoArgPlan>::type>::type;
+// An argument plan on the host, with the bytes of it in use.
+struct ArgPlanBuf {
+  ArgPlan plan;
+  size_t used;
+  bool small() const { return used <= kArgSmallBytes; }
+  const ArgPlanSmall& small_plan() const { return *reinterpret_cast<const ArgPlanSmall*>(plan.bytes); }
+};
 // Pointer to a plan array: at byte `off` of the argument plan, or `dev`.
-template <bool AP, class T>
+template <int AP, class T>
 __device__ __forceinline__ const T* plan_ptr(const PlanArg<AP>& ap, int32_t off, const T* dev) {
-  if constexpr (AP) return reinterpret_cast<const T*>(ap.bytes + off);
+  if constexpr (AP != kPlanInMemory) return reinterpret_cast<const T*>(ap.bytes + off);
   else return dev;
 }
 
@@ -146,18 +164,18 @@ void set_last_error(const char* msg);
 // Kernel launchers (each defined in the translation unit of its kernel).
 // `ap`: the plan in the kernel arguments (nullptr: read through p's pointers).
 hipError_t launch_extend_lds(const ExtendParams& p, int head_dim, int page_size, bool fp8,
-                             hipStream_t stream, const ArgPlan* ap = nullptr);
+                             hipStream_t stream, const ArgPlanBuf* ap = nullptr);
 hipError_t launch_extend_w64(const ExtendParams& p, int head_dim, int page_size, hipStream_t stream,
-                             const ArgPlan* ap = nullptr);
+                             const ArgPlanBuf* ap = nullptr);
 hipError_t launch_combine(const ExtendParams& p, int head_dim, int max_parts, hipStream_t stream,
-                          const ArgPlan* ap = nullptr);
+                          const ArgPlanBuf* ap = nullptr);
 hipError_t launch_decode(const ExtendParams& p, int head_dim, int page_size, bool fp8,
-                         hipStream_t stream, const ArgPlan* ap = nullptr);
+                         hipStream_t stream, const ArgPlanBuf* ap = nullptr);
 int decode_keys_per_tile(int head_dim, bool fp8);
 int decode_waves_per_cu(bool fp8);  // resident decode waves per CU (LDS-bound)
 // (the argument plan is the sequences alone, at its byte 0)
 hipError_t launch_write_pages(const WriteParams& p, int head_dim, int page_size, bool fp8,
-                              hipStream_t stream, const ArgPlan* ap = nullptr);
+                              hipStream_t stream, const ArgPlanBuf* ap = nullptr);
 hipError_t launch_swap(const SwapParams& p, hipStream_t stream);
 // Copies `bytes` from device-visible pinned host memory to device memory on
 // `stream` with a kernel (the plan upload).  With `done` (device address of

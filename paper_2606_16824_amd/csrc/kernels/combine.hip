@@ -35,7 +35,7 @@ __device__ __forceinline__ void load_part(const uint16_t* base, size_t elem, flo
 // each row's SLICES slices of 32 lanes fold every SLICES-th partial with an
 // online merge, then the slices are merged through LDS (SLICES = 1 for a few
 // partials per row, 8 for many).  Fixed order, no atomics.
-template <int D, int SLICES, bool AP>
+template <int D, int SLICES, int AP>
 __global__ __launch_bounds__(256) void combine_kernel(ExtendParams p, PlanArg<AP> ap) {
   constexpr int ROWS = 8 / SLICES;
   constexpr int PER = D / 32;  // dims per lane
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void combine_kernel(ExtendParams p, PlanArg<AP
   const int rsub = threadIdx.x / (32 * SLICES);
   const int lr = (blockIdx.x % wg_per_group) * ROWS + rsub;
   const CombineGroup cg = [&]() {
-    if constexpr (AP) {
+    if constexpr (AP != kPlanInMemory) {
       if (p.ap_desc > 0) {  // a decode plan in compact form: the group is rebuilt (each wave searches)
         const ExpandDesc& d = *reinterpret_cast<const ExpandDesc*>(ap.bytes + p.ap_desc);
         const DecodeRec* rec = reinterpret_cast<const DecodeRec*>(ap.bytes + d.rec_off);
@@ -175,15 +175,19 @@ __global__ __launch_bounds__(256) void combine_kernel(ExtendParams p, PlanArg<AP
 }  // namespace
 
 hipError_t launch_combine(const ExtendParams& p, int head_dim, int max_parts, hipStream_t stream,
-                          const ArgPlan* ap) {
+                          const ArgPlanBuf* ap) {
   if (p.n_groups <= 0) return hipSuccess;
   const bool many = max_parts > 4;
   const int rows_per_wg = many ? 1 : 8;
   const dim3 grid(p.n_groups * ((p.part_rows + rows_per_wg - 1) / rows_per_wg));
 #define CW_COMBINE(D_, S_)                                                                           \
   do {                                                                                               \
-    if (ap) hipLaunchKernelGGL((combine_kernel<D_, S_, true>), grid, dim3(256), 0, stream, p, *ap); \
-    else hipLaunchKernelGGL((combine_kernel<D_, S_, false>), grid, dim3(256), 0, stream, p, NoArgPlan{}); \
+    if (ap && ap->small())                                                                          \
+      hipLaunchKernelGGL((combine_kernel<D_, S_, kPlanInSmallArgs>), grid, dim3(256), 0, stream, p, ap->small_plan()); \
+    else if (ap)                                                                                    \
+      hipLaunchKernelGGL((combine_kernel<D_, S_, kPlanInArgs>), grid, dim3(256), 0, stream, p, ap->plan); \
+    else                                                                                            \
+      hipLaunchKernelGGL((combine_kernel<D_, S_, kPlanInMemory>), grid, dim3(256), 0, stream, p, NoArgPlan{}); \
   } while (0)
   if (head_dim == 64) {
     if (many) CW_COMBINE(64, 8);

@@ -50,6 +50,7 @@ constexpr float kNegBig = -1.0e30f;
 constexpr float kSumLimit = 65536.f;
 constexpr float kLn2 = 0.69314718055994531f;
 constexpr int kStages = 3;
+constexpr int kScalarSearchSeqs = 8;  // up to here an item's sequence is searched by scalar loads
 // K + V bytes of one tile: 16 KB for bf16 pools (three waves per CU), 8 KB for
 // fp8 pools, whose tiles cost twice the math per byte: six waves per CU (two
 // per SIMD) hide each other's MFMA and LDS latencies with the same bytes in
@@ -137,7 +138,7 @@ __device__ __forceinline__ int v_swz8(int row) {
   return RB == 128 ? 2 * ((row >> 1) & 3) : 2 * ((row >> 2) & 1);
 }
 
-template <int D, int P, bool FP8, bool AP>
+template <int D, int P, bool FP8, int AP>
 __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> ap) {
   using T = DGeo<D, P, FP8>;
   // one array per stage; the tile loop is unrolled by the stage count, so
@@ -148,15 +149,20 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
   __shared__ __attribute__((aligned(1024))) uint8_t lds_s2[T::TILE];
 
   WorkItem it;
-  if constexpr (AP) {
+  if constexpr (AP != kPlanInMemory) {
     // the plan in the kernel arguments, in compact form: this item is rebuilt
     // from the sequence records (the whole wave searches them)
     const ExpandDesc& d = *reinterpret_cast<const ExpandDesc*>(ap.bytes + p.ap_desc);
     const DecodeRec* rec = reinterpret_cast<const DecodeRec*>(ap.bytes + d.rec_off);
     const int i = blockIdx.x;
-    const int b_full = i < d.n_full ? wave_last_at_most(d.n_seqs, i, static_cast<int>(threadIdx.x),
-                                                        [&](int k) { return rec[k].full_off; })
-                                    : 0;
+    int b_full = 0;
+    if (i < d.n_full) {
+      if (d.n_seqs <= kScalarSearchSeqs) {
+        for (int k = 1; k < d.n_seqs; ++k) b_full += rec[k].full_off <= i ? 1 : 0;  // scalar loads
+      } else {
+        b_full = wave_last_at_most(d.n_seqs, i, static_cast<int>(threadIdx.x), [&](int k) { return rec[k].full_off; });
+      }
+    }
     it = expand_item_at(rec, reinterpret_cast<const int32_t*>(ap.bytes + d.tail_off), d, i, b_full);
   } else {
     it = p.items[blockIdx.x];
@@ -203,7 +209,13 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
   const bool writer = has_new && p.w.total_tokens > 0;
   int pg_new = 0;
   float ks_new = 1.f, vs_new = 1.f;
+  u32x4 kw = {0u, 0u, 0u, 0u}, vw = {0u, 0u, 0u, 0u};  // the writer lane's 16 bytes of the new row
   if (writer) {
+    if (lane < D / 8) {
+      const size_t src = (size_t(tok) * hkv + kvh) * (D / 8) + lane;
+      kw = static_cast<const u32x4*>(p.k_new)[src];
+      vw = static_cast<const u32x4*>(p.v_new)[src];
+    }
     pg_new = bt[lp / P];
     if constexpr (FP8) {
       const size_t si = size_t(pg_new) * hkv + kvh;
@@ -227,11 +239,34 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
     }
   }
 
+  // The new token's key and value, in the layouts that Q and O have.  They are read
+  // here, with Q, although they are used after the last tile: there their latency
+  // would end the item that usually ends the call (a decode of 1700 keys: 1 us).
+  bf16x8 k_own[T::KT];
+  bf16x4 v_own[T::DB][4];
+  if (has_new) {
+    const uint16_t* kn = static_cast<const uint16_t*>(p.k_new) + (size_t(tok) * hkv + kvh) * D;
+    const uint16_t* vn = static_cast<const uint16_t*>(p.v_new) + (size_t(tok) * hkv + kvh) * D;
+#pragma unroll
+    for (int kk = 0; kk < T::KT; ++kk) {
+      const int d0 = FP8 ? 32 * (kk >> 1) + 16 * h + 8 * (kk & 1) : 16 * kk + 8 * h;
+      k_own[kk] = *reinterpret_cast<const bf16x8*>(kn + d0);
+    }
+#pragma unroll
+    for (int b = 0; b < T::DB; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) v_own[b][q4] = *reinterpret_cast<const bf16x4*>(vn + 32 * b + 8 * q4 + 4 * h);
+  }
+
   // DMA: instruction j covers tile rows [j RPI, (j+1) RPI); lane fetches row
   // j RPI + lane / CPR into chunk position lane % CPR.  Rows past the chunk's
   // prefix end fetch the chunk's last key again (same page as the instruction's
   // first row, whose scores are masked), so every tile issues exactly 2 NI
-  // instructions and the vmcnt arithmetic below is exact.
+  // instructions and the vmcnt arithmetic below is exact.  No tile past the last is
+  // issued: refilling the stages with the chunk's last key up to the end kept one
+  // wait count for all steps but cost every item four or five tiles of DMA (a decode
+  // of 1700 keys, two tiles per item: 13.5 -> 11.8 us on the GPU; 96 decodes of
+  // 64-wide heads 110.3 -> 107.1 us; 48 fp8 decodes 279.5 -> 277.4 us).
   const int dma_row = lane / T::CPR, dma_pos = lane % T::CPR;
   auto issue_tile = [&](int t, uint32_t kdst) __attribute__((always_inline)) {
     const int j0 = kb + t * T::KPT;
@@ -261,11 +296,9 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
   // addresses need the ids), so only DMA is outstanding in the loop; this wait
   // is the compiler's own, so it knows that Q has landed.
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
-  if (n_tiles > 0) {
-    issue_tile(0, lds_addr(lds_s0));
-    issue_tile(1, lds_addr(lds_s1));
-    issue_tile(2, lds_addr(lds_s2));
-  }
+  if (n_tiles > 0) issue_tile(0, lds_addr(lds_s0));
+  if (n_tiles > 1) issue_tile(1, lds_addr(lds_s1));
+  if (n_tiles > 2) issue_tile(2, lds_addr(lds_s2));
   if constexpr (FP8) {
     my_lvs = __builtin_amdgcn_logf(my_vs);
     my_ivs = 1.f / my_vs;
@@ -395,38 +428,37 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
       }
     }
   };
-  // Tile t lives in stage t % 3.  Every step waits for its tile (the two
-  // issued after it may still fly), computes on it, then refills the stage with
-  // tile t + 3.  Steps past the last tile compute nothing, and issues past it
-  // fetch the chunk's last key again, so each step issues exactly 2 NI
-  // instructions and one fixed wait count holds everywhere.
+  // Tile t lives in stage t % 3.  A step waits for its tile (the two issued after it
+  // may still fly: 2 NI instructions each, fewer behind the last tiles), computes on
+  // it, then refills the stage with tile t + 3 if there is one.
   auto step = [&](int t, const uint8_t* st) __attribute__((always_inline)) {
-    wait_vmcnt<2 * 2 * T::NI>();
-    if (t < n_tiles) compute(t, st);
-    wait_lgkmcnt0();  // the stage's reads are done before it is refilled
-    issue_tile(t + 3, lds_addr(st));
+    const int behind = n_tiles - 1 - t;
+    if (behind >= 2) wait_vmcnt<2 * 2 * T::NI>();
+    else if (behind == 1) wait_vmcnt<2 * T::NI>();
+    else wait_vmcnt<0>();
+    compute(t, st);
+    if (behind >= 3) {
+      wait_lgkmcnt0();  // the stage's reads are done before it is refilled
+      issue_tile(t + 3, lds_addr(st));
+    }
   };
   for (int t = 0; t < n_tiles; t += 3) {
     step(t, lds_s0);
-    step(t + 1, lds_s1);
-    step(t + 2, lds_s2);
+    if (t + 1 < n_tiles) step(t + 1, lds_s1);
+    if (t + 2 < n_tiles) step(t + 2, lds_s2);
   }
   wait_vmcnt<0>();  // no DMA may land in LDS after the wave has ended
   if (writer && lane < D / 8)
-    pw::store_piece<D, P, FP8>(p.w, tok, kvh, lane, pg_new, lp % P, ks_new, vs_new);
+    pw::put_piece<D, P, FP8, false>(p.w, kw, vw, kvh, lane, pg_new, lp % P, ks_new, vs_new);
 
   // the new token's own key and value (bf16, from k_new / v_new)
   if (has_new) {
-    const uint16_t* kn = static_cast<const uint16_t*>(p.k_new) + (size_t(tok) * hkv + kvh) * D;
-    const uint16_t* vn = static_cast<const uint16_t*>(p.v_new) + (size_t(tok) * hkv + kvh) * D;
     float part = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < T::KT; ++kk) {
-      const int d0 = FP8 ? 32 * (kk >> 1) + 16 * h + 8 * (kk & 1) : 16 * kk + 8 * h;
-      const bf16x8 kv = *reinterpret_cast<const bf16x8*>(kn + d0);
+    for (int kk = 0; kk < T::KT; ++kk)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) part = fmaf(static_cast<float>(qf[kk][e]), static_cast<float>(kv[e]), part);
-    }
+      for (int e = 0; e < 8; ++e)
+        part = fmaf(static_cast<float>(qf[kk][e]), static_cast<float>(k_own[kk][e]), part);
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
     const float x = (__uint_as_float(sw[0]) + __uint_as_float(sw[1])) * c;
     const float m_new = fmaxf(m_run, x);
@@ -439,9 +471,9 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
     for (int b = 0; b < T::DB; ++b) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const bf16x4 v4 = *reinterpret_cast<const bf16x4*>(vn + 32 * b + 8 * q4 + 4 * h);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[b][4 * q4 + e] = fmaf(pb, static_cast<float>(v4[e]), o[b][4 * q4 + e] * alpha);
+        for (int e = 0; e < 4; ++e)
+          o[b][4 * q4 + e] = fmaf(pb, static_cast<float>(v_own[b][q4][e]), o[b][4 * q4 + e] * alpha);
       }
     }
   }
@@ -485,9 +517,14 @@ __global__ __launch_bounds__(64) void decode_kernel(ExtendParams p, PlanArg<AP> 
 }
 
 template <int D, int P, bool FP8>
-hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlan* ap) {
-  if (ap) hipLaunchKernelGGL((decode_kernel<D, P, FP8, true>), dim3(p.n_items), dim3(64), 0, stream, p, *ap);
-  else hipLaunchKernelGGL((decode_kernel<D, P, FP8, false>), dim3(p.n_items), dim3(64), 0, stream, p, NoArgPlan{});
+hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlanBuf* ap) {
+  const dim3 grid(p.n_items), block(64);
+  if (ap != nullptr && ap->small())
+    hipLaunchKernelGGL((decode_kernel<D, P, FP8, kPlanInSmallArgs>), grid, block, 0, stream, p, ap->small_plan());
+  else if (ap != nullptr)
+    hipLaunchKernelGGL((decode_kernel<D, P, FP8, kPlanInArgs>), grid, block, 0, stream, p, ap->plan);
+  else
+    hipLaunchKernelGGL((decode_kernel<D, P, FP8, kPlanInMemory>), grid, block, 0, stream, p, NoArgPlan{});
   return hipGetLastError();
 }
 
@@ -500,7 +537,7 @@ int decode_keys_per_tile(int head_dim, bool fp8) { return tile_bytes(fp8) / (2 *
 int decode_waves_per_cu(bool fp8) { return (160 * 1024) / (kStages * tile_bytes(fp8)); }  // 160 KB of LDS per CU
 
 hipError_t launch_decode(const ExtendParams& p, int head_dim, int page_size, bool fp8,
-                         hipStream_t stream, const ArgPlan* ap) {
+                         hipStream_t stream, const ArgPlanBuf* ap) {
   if (p.n_items <= 0) return hipSuccess;
 #define CW_CASE(D_, P_)                                                                   \
   if (head_dim == D_ && page_size == P_)                                                  \

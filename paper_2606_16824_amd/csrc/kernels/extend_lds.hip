@@ -182,7 +182,7 @@ struct LGeo {
   static_assert(NI * RPI == 8, "each wave stages 8 rows of a tile");
 };
 
-template <int D, int P, bool FP8, bool AP>
+template <int D, int P, bool FP8, int AP>
 __global__ __launch_bounds__(LDS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 void extend_lds_kernel(ExtendParams p, PlanArg<AP> ap) {
   using T = LGeo<D, P, FP8>;
@@ -808,19 +808,21 @@ void extend_lds_kernel(ExtendParams p, PlanArg<AP> ap) {
 }
 
 template <int D, int P, bool FP8>
-hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlan* ap) {
-  if (ap != nullptr)
-    hipLaunchKernelGGL((extend_lds_kernel<D, P, FP8, true>), dim3(p.n_items), dim3(LDS_THREADS), 0, stream, p, *ap);
+hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlanBuf* ap) {
+  const dim3 grid(p.n_items), block(LDS_THREADS);
+  if (ap != nullptr && ap->small())
+    hipLaunchKernelGGL((extend_lds_kernel<D, P, FP8, kPlanInSmallArgs>), grid, block, 0, stream, p, ap->small_plan());
+  else if (ap != nullptr)
+    hipLaunchKernelGGL((extend_lds_kernel<D, P, FP8, kPlanInArgs>), grid, block, 0, stream, p, ap->plan);
   else
-    hipLaunchKernelGGL((extend_lds_kernel<D, P, FP8, false>), dim3(p.n_items), dim3(LDS_THREADS), 0, stream, p,
-                       NoArgPlan{});
+    hipLaunchKernelGGL((extend_lds_kernel<D, P, FP8, kPlanInMemory>), grid, block, 0, stream, p, NoArgPlan{});
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_extend_lds(const ExtendParams& p, int head_dim, int page_size, bool fp8,
-                             hipStream_t stream, const ArgPlan* ap) {
+                             hipStream_t stream, const ArgPlanBuf* ap) {
   if (p.n_items <= 0) return hipSuccess;
 #define CW_LDS_CASE(D_, P_)                                                        \
   if (head_dim == D_ && page_size == P_)                                           \

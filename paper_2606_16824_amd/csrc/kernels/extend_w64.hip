@@ -656,9 +656,9 @@ void extend_w64_kernel(ExtendParams p, PlanArg<AP> ap) {
 }
 
 template <int D, int P>
-hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlan* ap) {
+hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlanBuf* ap) {
   if (ap != nullptr)
-    hipLaunchKernelGGL((extend_w64_kernel<D, P, true>), dim3(p.n_items), dim3(kThreads), 0, stream, p, *ap);
+    hipLaunchKernelGGL((extend_w64_kernel<D, P, true>), dim3(p.n_items), dim3(kThreads), 0, stream, p, ap->plan);
   else
     hipLaunchKernelGGL((extend_w64_kernel<D, P, false>), dim3(p.n_items), dim3(kThreads), 0, stream, p,
                        NoArgPlan{});
@@ -668,7 +668,7 @@ hipError_t launch_t(const ExtendParams& p, hipStream_t stream, const ArgPlan* ap
 }  // namespace
 
 hipError_t launch_extend_w64(const ExtendParams& p, int head_dim, int page_size, hipStream_t stream,
-                             const ArgPlan* ap) {
+                             const ArgPlanBuf* ap) {
   if (p.n_items <= 0) return hipSuccess;
   if (head_dim == 64 && page_size == 16) return launch_t<64, 16>(p, stream, ap);
   if (head_dim == 64 && page_size == 64) return launch_t<64, 64>(p, stream, ap);

@@ -33,7 +33,7 @@ constexpr int kPieces = 2;  // 16-byte pieces of K and of V per lane and pass
 constexpr int kThreads = 256;
 constexpr int kWavePieces = 64 * kPieces;
 
-template <int D, int P, bool FP8, bool AP>
+template <int D, int P, bool FP8, int AP>
 __global__ __launch_bounds__(kThreads) void write_pages_kernel(WriteParams p, PlanArg<AP> ap) {
   constexpr int CH = D / 8;  // pieces per (token, kv head) row
   const SeqInfo* seqs = plan_ptr<AP>(ap, 0, p.seqs);
@@ -95,22 +95,26 @@ __global__ __launch_bounds__(kThreads) void write_pages_kernel(WriteParams p, Pl
 }
 
 template <int D, int P, bool FP8>
-hipError_t launch_t(const WriteParams& p, hipStream_t stream, const ArgPlan* ap) {
+hipError_t launch_t(const WriteParams& p, hipStream_t stream, const ArgPlanBuf* ap) {
   const int64_t total = int64_t(p.total_tokens) * p.num_kv_heads * (D / 8);
   constexpr int kBlockPieces = kThreads / 64 * kWavePieces;
   const int64_t blocks = std::min<int64_t>((total + kBlockPieces - 1) / kBlockPieces, 65536);
   const dim3 grid(static_cast<unsigned>(blocks));
-  if (ap != nullptr)
-    hipLaunchKernelGGL((write_pages_kernel<D, P, FP8, true>), grid, dim3(kThreads), 0, stream, p, *ap);
+  if (ap != nullptr && ap->small())
+    hipLaunchKernelGGL((write_pages_kernel<D, P, FP8, kPlanInSmallArgs>), grid, dim3(kThreads), 0, stream, p,
+                       ap->small_plan());
+  else if (ap != nullptr)
+    hipLaunchKernelGGL((write_pages_kernel<D, P, FP8, kPlanInArgs>), grid, dim3(kThreads), 0, stream, p, ap->plan);
   else
-    hipLaunchKernelGGL((write_pages_kernel<D, P, FP8, false>), grid, dim3(kThreads), 0, stream, p, NoArgPlan{});
+    hipLaunchKernelGGL((write_pages_kernel<D, P, FP8, kPlanInMemory>), grid, dim3(kThreads), 0, stream, p,
+                       NoArgPlan{});
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_write_pages(const WriteParams& p, int head_dim, int page_size, bool fp8,
-                              hipStream_t stream, const ArgPlan* ap) {
+                              hipStream_t stream, const ArgPlanBuf* ap) {
   if (p.total_tokens <= 0) return hipSuccess;
 #define CW_CASE(D_, P_)                                                                          \
   if (head_dim == D_ && page_size == P_)                                                         \
