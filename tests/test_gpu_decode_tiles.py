@@ -70,3 +70,20 @@ def test_plan_sizes(n):
     lp = [(37 * i) % 200 for i in range(n)]
     print(f"\n[case] decode plan sizes {n}", flush=True)
     _check(lp, 1, 4, 64, 16, "bf16", 109, f"{n} sequences")
+
+
+@pytest.mark.parametrize("d,p", [(128, 16), (64, 64)])
+@pytest.mark.parametrize("parts", [[4, 1, 2], [5, 2], [64, 17, 16, 15], [65, 3, 64], [128, 33], [129, 1, 31], [300, 256, 257]])
+def test_merge_counts(d, p, parts):
+    """Rows of up to 4, 64, 128 and more partials (another merge kernel or another
+    batch size beyond each), with rows of fewer partials in the same call."""
+    keys = KEYS[("bf16", d)]
+    lp = [n * keys - 1 - (i % 3) for i, n in enumerate(parts)]
+    print(f"\n[case] merge of {parts} partials d={d}", flush=True)
+    cwlib.set_tuning(0, 1)
+    try:
+        items, groups = cwlib.decode_plan(lp, 2, 5, d, p)
+        assert sorted(set(groups[:, 5].tolist())) == sorted(set(n for n in parts if n > 1))
+        _check(lp, 2, 5, d, p, "bf16", 113, f"merge of {parts} partials d={d}")
+    finally:
+        cwlib.set_tuning(0, 0)
