@@ -40,7 +40,7 @@
  *
  * Ownership and ordering: the caller owns every buffer, including the
  * workspace.  Per device the library keeps a cache of device properties, a
- * pinned host staging ring for the per-call plan (8 slots of 4 MiB and 64 KiB, allocated
+ * pinned host staging ring for the per-call plan (8 slots of about 4 MiB, allocated
  * once by cw_init or by the first call that needs it, never grown or freed;
  * a call whose plan exceeds a slot fails with CW_ERR_UNSUPPORTED) and the
  * static scratch array of cw_extend_attention_noalloc.  No call allocates

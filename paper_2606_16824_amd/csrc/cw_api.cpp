@@ -76,17 +76,17 @@ constexpr int kMaxDevices = 64;
 constexpr int kStagingSlots = 8;
 // Every staging slot has this fixed size, allocated once per device (cw_init or
 // the first call that uploads a plan).  A plan whose size before levelling is more
-// than kMaxPlanBytes is rejected; levelling adds at most kLevelMetaBytes.
+// than kMaxPlanBytes is rejected; levelling adds at most 2 kLevelMetaBytes.
 // The last bytes of a slot are the words its upload kernel's workgroups write
 // once they have read the slot (one per workgroup); the plan gets the rest.
 constexpr size_t kDoneBytes = size_t(kMaxUploadWorkgroups) * sizeof(uint32_t);
 constexpr size_t kMaxPlanBytes = (size_t(4) << 20) - kDoneBytes;
-constexpr size_t kPlanSlotBytes = kMaxPlanBytes + kLevelMetaBytes;
+constexpr size_t kPlanSlotBytes = kMaxPlanBytes + 2 * kLevelMetaBytes;  // (a step has an extend and a decode plan)
 constexpr size_t kStagingSlotBytes = kPlanSlotBytes + kDoneBytes;
 // A call captured into a graph carries its plan in kernel arguments (2 KiB per
 // copy launch); its plan may take at most this many bytes before levelling.
 constexpr size_t kCaptureMaxBytes = size_t(256) << 10;
-constexpr size_t kCaptureBufBytes = kCaptureMaxBytes + kLevelMetaBytes;
+constexpr size_t kCaptureBufBytes = kCaptureMaxBytes + 2 * kLevelMetaBytes;
 
 struct StagingSlot {
   void* host = nullptr;
@@ -1014,8 +1014,8 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
   };
   const bool arg_plan =
       arg_plans() && (sp.dec.empty() || (sp.ext.empty() && compact && compact_arg_fits(cu)));
-  return stage_and_launch(sp.meta_bytes, sp.meta_bytes - sp.ext_plan.meta_bytes + sp.ext_plan.whole_meta_bytes, ws,
-                          stream, [&](uint8_t* h) {
+  const size_t whole_bytes = sp.off_ext_meta + sp.ext_plan.whole_meta_bytes + sp.dec_plan.whole_meta_bytes;
+  return stage_and_launch(sp.meta_bytes, whole_bytes, ws, stream, [&](uint8_t* h) {
     head(h);
     if (!sp.dec.empty()) pack_plan_meta(sp.dec_plan, h + sp.off_dec_meta);
   }, launch, false, plan_direct(false), compact ? &cu : nullptr, [&](uint8_t* h) {

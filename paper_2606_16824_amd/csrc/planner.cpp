@@ -610,13 +610,69 @@ void layout_workspace(ExtendPlan& plan, int32_t head_dim) {
 }
 }  // namespace
 
+namespace {
+// Items and merge groups of a decode cut into chunks of `chunk` keys.
+std::pair<int64_t, int64_t> decode_counts(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv_heads,
+                                          int64_t chunk) {
+  int64_t items = 0, groups = 0;
+  for (int32_t b = 0; b < num_seqs; ++b) {
+    const int64_t n_c = (int64_t(prefix_lens[b]) + chunk) / chunk;  // of prefix_lens[b] + 1 keys
+    items += n_c;
+    groups += n_c > 1 ? 1 : 0;
+  }
+  return {items * num_kv_heads, groups * num_kv_heads};
+}
+
+// The chunk length (keys) that fills whole rounds of the GPU.  Where one round can
+// hold the call, that is the shortest chunk with at most four items per CU (three, the
+// resident ones, for bf16 pools); where the longest chunk gives up to four rounds, the
+// shortest with that many.  A round that is partly filled costs nearly a full one,
+// because a wave alone on its CU takes about half the time per tile of one among
+// three: too little to make up for the empty slots.  Measured with 8 kv heads of 128:
+// bf16 pools, 8 prefixes of 2k-32k: 1072 items (1.4 rounds) 102 us, 1536 items 92 us;
+// 12 of 8k-30k: 1592 items 147 us, 2296 items 132 us; 16 of 1k-16k: 824 items 82 us, 728
+// items 76 us.  fp8 pools, 2 of 30k-50k: 1512 items (six per CU) 37.4 us, 984 items 33.0
+// us, 760 items 33.2 us; 4 of 20k-60k: 1080 items 61 us, 1520 items 54 us; 24 of 3k-20k:
+// 1984 items 108 us, 2976 items 94 us.  Beyond four rounds the longest chunk is best
+// (48 decodes over fp8 pages: 6464 items 278 us, 7400 items 280 us).  Where more than
+// half of the items are the last, shorter chunks of their sequences, no chunk length
+// makes them even, and `plain` stays (96 prefixes of 200-6000 keys, 64-wide heads: 107 us
+// with it, 111-117 us with 1100-1500 items).
+int64_t round_chunk(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv_heads, int64_t unit,
+                    int64_t max_chunk, int64_t min_chunk, int64_t num_cus, int64_t waves_per_cu, int64_t plain) {
+  auto items = [&](int64_t chunk) { return decode_counts(prefix_lens, num_seqs, num_kv_heads, chunk).first; };
+  const int64_t slots = num_cus * waves_per_cu, one_round = num_cus * std::min<int64_t>(waves_per_cu, 4);
+  const int64_t longest = max_chunk / unit * unit;
+  const int64_t least = items(longest);
+  int64_t most = std::max(one_round, least);  // (2% over: 1040 items for 1024 29.5 us, 1480 items 33.8 us)
+  if (least * 50 > one_round * 51) {
+    const int64_t rounds = (least + slots - 1) / slots;
+    if (rounds > 4) return plain;
+    most = rounds * slots;
+  }
+  int64_t lo = min_chunk / unit, hi = longest / unit;  // items(hi) <= most; items never rise with the chunk
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (items(mid * unit) <= most) hi = mid;
+    else lo = mid + 1;
+  }
+  const auto n = decode_counts(prefix_lens, num_seqs, num_kv_heads, lo * unit);
+  const auto n_plain = decode_counts(prefix_lens, num_seqs, num_kv_heads, plain);
+  if (int64_t(num_seqs) * num_kv_heads * 2 > n.first) return plain;
+  // the larger work list stays within what the limits on a call's plan allow for
+  if ((n.first - n_plain.first + n.second - n_plain.second + 24) * int64_t(sizeof(WorkItem)) > int64_t(kLevelMetaBytes))
+    return plain;
+  return lo * unit;
+}
+}  // namespace
+
 // Decode planning.  The cached prefix of each (sequence, kv head) is cut into
 // chunks of whole decode tiles and whole pages (at most 64 pages, the kernel
-// keeps one page id per lane).  Chunks are as long as one wave per resident
+// keeps one page id per lane).  Chunks are about as long as one wave per resident
 // slot allows (a decode wave streams its chunk at its share of HBM bandwidth;
 // every wave pays one start-up latency for its page ids and first tile, so
-// fewer, longer waves waste less), within the 64-page cap.  The new token's
-// own key rides with the last chunk.
+// fewer, longer waves waste less), within the 64-page cap, adjusted to whole
+// rounds of the GPU (round_chunk).  The new token's own key rides with the last chunk.
 ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv_heads,
                              int32_t gqa_group, int32_t head_dim, int32_t page_size,
                              int32_t keys_per_tile, int32_t waves_per_cu, int32_t num_cus,
@@ -640,6 +696,11 @@ ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32
     chunk = tiles * keys_per_tile;
   }
   chunk = std::min(max_chunk, std::max(unit, (chunk + unit - 1) / unit * unit));
+  const int64_t plain_chunk = chunk;
+  if (tuning.kv_chunk_tiles == 0 && tuning.target_wgs == 0)
+    chunk = round_chunk(prefix_lens, num_seqs, num_kv_heads, unit, max_chunk,
+                        std::max<int64_t>(unit, (2 * int64_t(keys_per_tile) + unit - 1) / unit * unit), num_cus,
+                        waves_per_cu, plain_chunk);
   // Longest chunks first so that short tails fill in at the end: every chunk but
   // the last of a (sequence, kv head) has the full length, so the order is the
   // full-length chunks in build order, then the shorter last chunks by length
@@ -673,6 +734,10 @@ ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32
   plan.items.insert(plan.items.end(), tails.begin(), tails.end());
   layout_workspace(plan, head_dim);
   plan.whole_meta_bytes = plan.meta_bytes;
+  if (chunk != plain_chunk) {
+    const auto n = decode_counts(prefix_lens, num_seqs, num_kv_heads, plain_chunk);
+    plan.whole_meta_bytes = plan_meta_bytes(plan.seqs.size(), static_cast<size_t>(n.first), static_cast<size_t>(n.second));
+  }
 
   // the compact form: one record per sequence, the order of the last chunks
   plan.compact = true;

@@ -40,8 +40,9 @@ struct ExtendPlan {
   // Workspace layout (byte offsets, 256-byte aligned).
   size_t off_seqs = 0, off_items = 0, off_groups = 0, off_part_o = 0, off_part_ml = 0;
   size_t meta_bytes = 0;  // seqs + items + groups: the part uploaded per call
-  // extend plans: meta_bytes of the plan before levelling.  The limits on a call's
-  // plan are limits on this, so that levelling refuses nothing.
+  // meta_bytes of the plan before levelling (extends) or with chunks not adjusted to
+  // whole rounds (decodes); both add at most kLevelMetaBytes.  The limits on a call's
+  // plan are limits on this, so that neither refuses a call.
   size_t whole_meta_bytes = 0;
   size_t total_bytes = 0;
   int32_t part_rows = 0;  // rows per partial slot

@@ -174,3 +174,34 @@ def test_levelled_plan(lp, ls, hkv, g, cut):
     assert finish_times(whole, lp).max() > 1.04 * t.max()
     n_groups = len(np.unique(parts[:, :3], axis=0))
     assert len(items) * 32 + n_groups * 32 <= len(whole) * 32 + (64 << 10)
+
+
+RAGGED = [400 + 9 * i for i in range(300)]
+_MEAN = -(-sum((x + 32) // 32 * 8 for x in RAGGED) // 768) * 32  # keys of one of 768 equal shares
+N_RAGGED = sum((x + _MEAN) // _MEAN * 8 for x in RAGGED)
+
+
+# (prefix lens, kv heads, pool, items): one round of at most three waves per CU for
+# bf16 pools and four for fp8; two and three rounds of the resident waves where the
+# longest chunk (64 pages) needs more than one; one sequence a little over a round;
+# more than four rounds (the longest chunk); mostly last chunks (chunk of the mean)
+@pytest.mark.parametrize("lp,hkv,dt,lo,hi", [
+    ([32000], 8, "bf16", 600, 768), ([32000], 8, "fp8", 900, 1024),
+    ([40000, 30000, 20000], 8, "fp8", 900, 1024), ([60000, 70000], 2, "bf16", 700, 768),
+    ([20000] * 8, 8, "bf16", 1400, 1536), ([20000] * 12, 8, "bf16", 2000, 2304),
+    ([16000] * 24, 8, "fp8", 2600, 3072), ([30000] * 6, 8, "fp8", 1400, 1536),
+    ([30000] * 40, 8, "bf16", 40 * 8 * 30, 40 * 8 * 30), (RAGGED, 8, "bf16", N_RAGGED, N_RAGGED),
+])
+def test_decode_chunks_fill_rounds(lp, hkv, dt, lo, hi):
+    items, groups = cwlib.decode_plan(lp, hkv, 4, 128, 16, dt)
+    assert lo <= len(items) <= hi, len(items)
+    keys = items[:, 4] - items[:, 3]
+    assert keys.max() <= 64 * 16
+    # every chunk but a sequence's last has the same length
+    last = {}
+    for s, h, _, kb, ke, *_ in items.tolist():
+        last[(s, h)] = max(last.get((s, h), 0), ke)
+    full = [ke - kb for s, h, _, kb, ke, *_ in items.tolist() if ke != last[(s, h)]]
+    assert len(set(full)) <= 1
+    rebuilt, rebuilt_groups = cwlib.decode_plan(lp, hkv, 4, 128, 16, dt, rebuilt=True)
+    assert np.array_equal(items, rebuilt) and np.array_equal(groups, rebuilt_groups)
