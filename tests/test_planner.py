@@ -176,8 +176,8 @@ def test_levelled_plan(lp, ls, hkv, g, cut):
     assert len(items) * 32 + n_groups * 32 <= len(whole) * 32 + (64 << 10)
 
 
-RAGGED = [400 + 9 * i for i in range(300)]
-_MEAN = -(-sum((x + 32) // 32 * 8 for x in RAGGED) // 768) * 32  # keys of one of 768 equal shares
+RAGGED = [100 + 9 * i for i in range(100)]
+_MEAN = -(-sum((x + 32) // 32 * 8 for x in RAGGED) // 768) * 32  # keys of one of 768 equal shares (below 64 pages)
 N_RAGGED = sum((x + _MEAN) // _MEAN * 8 for x in RAGGED)
 
 
