@@ -57,7 +57,8 @@
  * replay; either way a replay runs with the plan it was captured with, and
  * the lengths are those of capture time.  cw_init() must have been called on
  * the device first (CW_ERR_INIT), and a plan that goes through the copy
- * kernels may take at most 256 KiB (CW_ERR_UNSUPPORTED beyond).  The buffers of a captured
+ * kernels may take at most 256 KiB (CW_ERR_UNSUPPORTED beyond; as for the staging
+ * slot, without what levelling its work adds).  The buffers of a captured
  * call must stay valid while the graph may be replayed, and a replay shares
  * its workspace (or the no-alloc scratch) with every other call using it, as
  * any call on the graph's stream would.
