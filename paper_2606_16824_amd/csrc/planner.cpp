@@ -195,7 +195,7 @@ bool level_queues(const std::vector<Tile>& tiles, const std::vector<std::vector<
   queues.assign(X, {});
   for (size_t x = 0; x < X; ++x) {
     for (size_t i = 0; i < owned[x].size(); ++i) pos[owned[x][i]] = static_cast<int32_t>(i);
-    if (as_before[x]) {  // the same costs as the queue before: the same pieces of its own tiles
+    if (as_before[x]) {  // tiles shaped like the queue's before: the same pieces of its own tiles
       slots[x] = slots[x - 1];
       next[x] = next[x - 1];
       for (const Piece& p : queues[x - 1])
@@ -300,7 +300,12 @@ void level_plan(ExtendPlan& plan, const std::vector<Tile>& tiles, const std::vec
     mine[x].push_back(&bd);
   }
   std::vector<std::vector<int32_t>> owned(X);
-  std::vector<bool> as_before(X, false);  // queue x has the same costs in the same order as queue x - 1
+  // queue x's tiles are shaped like queue x - 1's, one by one, so the same key ranges level it
+  // (equal costs would not do: a full tile and a longer one of fewer rows may cost the same)
+  std::vector<bool> as_before(X, false);
+  auto shaped_alike = [&](int32_t a, int32_t c) {
+    return tiles[a].n_kt == tiles[c].n_kt && tiles[a].n_pre == tiles[c].n_pre && tiles[a].rows == tiles[c].rows;
+  };
   std::vector<int64_t> costs, last;
   int64_t ordered = 0, last_span = 0;
   for (size_t x = 0; x < X; ++x) {
@@ -314,8 +319,9 @@ void level_plan(ExtendPlan& plan, const std::vector<Tile>& tiles, const std::vec
         costs.push_back(tile_cost(tiles[owned[x].back()], wgt));
       }
     }
-    as_before[x] = x > 0 && costs == last;
-    if (!as_before[x]) {
+    as_before[x] = x > 0 && std::equal(owned[x].begin(), owned[x].end(), owned[x - 1].begin(), owned[x - 1].end(),
+                                       shaped_alike);
+    if (costs != last) {
       last_span = list_makespan(costs, R);
       last.swap(costs);
     }

@@ -1,15 +1,18 @@
 """GPU extend with a levelled plan: query tiles cut at key ranges of unequal length
 so that all workgroups finish together.  Against the same call with whole tiles
 (a target of 256 workgroups in the place of the automatic plan), whose parity the
-other tests pin: the split-K merge may move a result by up to two bf16 ulps.  The
-no-alloc call and a captured call run the same plan bit for bit."""
+other tests pin: the split-K merge may move a result by up to two bf16 ulps; and, for
+tiles that cost the same but differ in shape, against the oracle.  The no-alloc call
+and a captured call run the same plan bit for bit."""
 import numpy as np
 import pytest
 import torch
 
 import cw_workloads as cw
+import oracle
 import paper_2606_16824_amd as cwlib
-from gpu_util import as_f64, assert_close, assert_within_bf16_ulps, bits, run_extend, to_gpu
+from conftest import paged_inputs
+from gpu_util import BF16_MAX_ABS, BF16_MEAN_ABS, as_f64, assert_close, assert_within_bf16_ulps, bits, run_extend, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +23,8 @@ CASES = {
                                   d=128, p=16, dt="bf16"),
     "replies_d64": dict(lp=[19000, 31000, 5000, 12000, 27000, 9000, 30000, 8001],
                         ls=[598, 59, 14, 66, 154, 15, 542, 402], hkv=8, g=4, d=64, p=64, dt="bf16"),
+    # full tiles and longer ones of 32 rows that cost the same
+    "equal_cost": dict(lp=[3632, 5120] * 33, ls=[32, 4] * 33, hkv=4, g=8, d=64, p=16, dt="bf16"),
     "mqa_fp8": dict(lp=[40000, 39990, 40010, 17, 40005], ls=[700, 699, 701, 5, 703], hkv=1, g=16, d=128, p=16, dt="fp8"),
 }
 
@@ -32,8 +37,13 @@ def test_levelled_against_whole_tiles(name):
     print(f"\n[case] levelled {name}: {c}", flush=True)
     items = cwlib.plan_items(spec.prefix_lens, spec.suffix_lens, c["hkv"], c["g"], c["d"], c["p"])
     assert (items[:, 5] >= 0).any()
-    dw = to_gpu(cw.materialize(spec))
+    w = cw.materialize(spec)
+    dw = to_gpu(w)
     out, lse = run_extend(dw)
+    if name == "equal_cost":  # small enough for the oracle
+        ref, ref_lse = oracle.extend_attention_blocked(paged_inputs(w))
+        assert_close(as_f64(out), ref, BF16_MAX_ABS, BF16_MEAN_ABS, "levelled " + name)
+        assert_close(lse.cpu().double().numpy(), ref_lse, 1e-2, None, "levelled " + name + " lse")
     cwlib.set_tuning(1, 256)
     try:
         whole, whole_lse = run_extend(dw)

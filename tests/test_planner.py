@@ -176,6 +176,50 @@ def test_levelled_plan(lp, ls, hkv, g, cut):
     assert len(items) * 32 + n_groups * 32 <= len(whole) * 32 + (64 << 10)
 
 
+def equal_cost_kinds(rng, g, n_kinds):
+    """Two to n_kinds sequences (prefix, new tokens) of one query tile each whose tiles cost the same in
+    the planner's units but differ in key tiles or rows."""
+    by_cost = {}
+    for ls in range(1, BM // g + 1):
+        for pre in range(40, 260):
+            n_kt = -(-(pre * BN + ls) // BN)
+            by_cost.setdefault((pre * 100 + (n_kt - pre) * 125) * RATE[(ls * g - 1) // 32] // 100, []).append((pre, ls))
+    buckets = [k for cost, k in sorted(by_cost.items()) if cost >= 5000 and len({pre for pre, _ in k}) >= 2]
+    kinds = {}
+    for pre, ls in rng.permutation(buckets[rng.integers(len(buckets))]).tolist():
+        kinds.setdefault(pre, (pre * BN, ls))
+    return list(kinds.values())[:n_kinds]
+
+
+# Tiles of one cost and several shapes: neighbouring queues then look alike by their costs.
+@pytest.mark.parametrize("kinds,n,hkv,g", [
+    ([(11680, 64), (16320, 8)], 264, 1, 4),
+    ([(11704, 16), (16320, 2)], 136, 2, 16),
+    ([(11696, 32), (16320, 4)], 66, 4, 8),
+    ([(7072, 64), (9920, 32)], 66, 4, 4),
+    ([(9920, 32), (7072, 64)], 66, 4, 4),
+    ([(3632, 32), (5120, 4)], 66, 4, 8),
+])
+def test_levelled_plan_tiles_of_equal_cost(kinds, n, hkv, g):
+    seqs = [kinds[i % len(kinds)] for i in range(n)]
+    items = check_plan(np.array([a for a, _ in seqs]), np.array([b for _, b in seqs]), hkv, g)
+    assert (items[:, 5] >= 0).any()  # tiles were cut
+
+
+@pytest.mark.parametrize("hkv", [1, 2, 3, 4, 5, 8, 16])
+def test_levelled_plan_tiles_of_equal_cost_generated(hkv):
+    rng = np.random.default_rng(131 + hkv)
+    cut = 0
+    for _ in range(12):
+        g = int(rng.choice([1, 4, 8, 16]))
+        kinds = equal_cost_kinds(rng, g, int(rng.integers(2, 4)))
+        n = -(-int(rng.integers(257, 420)) // hkv)
+        seqs = [kinds[i % len(kinds)] for i in range(n)]
+        items = check_plan(np.array([a for a, _ in seqs]), np.array([b for _, b in seqs]), hkv, g)
+        cut += bool((items[:, 5] >= 0).any())
+    assert cut >= 6
+
+
 RAGGED = [100 + 9 * i for i in range(100)]
 _MEAN = -(-sum((x + 32) // 32 * 8 for x in RAGGED) // 768) * 32  # keys of one of 768 equal shares (below 64 pages)
 N_RAGGED = sum((x + _MEAN) // _MEAN * 8 for x in RAGGED)
