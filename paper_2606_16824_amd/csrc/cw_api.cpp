@@ -26,6 +26,7 @@
 // host code this name is only a stand-in; kernels get the device address that
 // hipGetSymbolAddress returns for the current device (DeviceState::scratch).
 static __device__ __align__(256) uint8_t scratch[CW_NOALLOC_SCRATCH_BYTES];
+static_assert(cw::kLevelTotalBytes <= int64_t(CW_NOALLOC_SCRATCH_BYTES), "levelling refuses no no-alloc call");
 
 namespace cw {
 namespace {
@@ -668,11 +669,12 @@ ExtendParams plan_params(const ExtendPlan& plan, const uint8_t* meta, uint8_t* w
     p.items = reinterpret_cast<const WorkItem*>(meta + plan.off_items);
     p.groups = reinterpret_cast<const CombineGroup*>(meta + plan.off_groups);
   }
-  p.part_o = reinterpret_cast<uint16_t*>(ws + part + (plan.off_part_o - plan.meta_bytes));
+  p.part_o = ws + part + (plan.off_part_o - plan.meta_bytes);
   p.part_ml = reinterpret_cast<float*>(ws + part + (plan.off_part_ml - plan.meta_bytes));
   p.n_items = static_cast<int32_t>(plan.items.size());
   p.n_groups = static_cast<int32_t>(plan.groups.size());
   p.part_rows = plan.part_rows;
+  p.part_f32 = plan.part_f32 ? 1 : 0;
   return p;
 }
 
@@ -732,7 +734,7 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
   p.block_table = block_table;
   p.out = out;
   p.lse = lse;
-  p.part_o = reinterpret_cast<uint16_t*>(ws + plan.off_part_o);
+  p.part_o = ws + plan.off_part_o;
   p.part_ml = reinterpret_cast<float*>(ws + plan.off_part_ml);
   p.bt_stride = bt_stride;
   p.num_kv_heads = num_kv_heads;
@@ -742,6 +744,7 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
   p.n_items = static_cast<int32_t>(plan.items.size());
   p.n_groups = static_cast<int32_t>(plan.groups.size());
   p.part_rows = plan.part_rows;
+  p.part_f32 = plan.part_f32 ? 1 : 0;
   if (write_pages) {
     p.w.k_new = k_new;
     p.w.v_new = v_new;

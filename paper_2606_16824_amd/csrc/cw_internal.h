@@ -120,7 +120,7 @@ struct ExtendParams {
   const SeqInfo* seqs;
   const WorkItem* items;
   const CombineGroup* groups;
-  uint16_t* part_o;  // [n_parts, part_rows, D] bf16: the unnormalised partial O
+  void* part_o;    // [n_parts, part_rows, D]: the unnormalised partial O, fp32 or bf16 (part_f32)
   float* part_ml;  // [n_parts, part_rows, 2]  (running max in log2 units, sum)
   int32_t bt_stride;
   int32_t num_kv_heads;
@@ -130,6 +130,7 @@ struct ExtendParams {
   int32_t n_items;
   int32_t n_groups;
   int32_t part_rows;  // rows per split-K partial slot (the row block for extend, G for decode)
+  int32_t part_f32;   // 1: part_o is fp32, 0: bf16
   // with an argument plan: byte offsets in it of seqs, items, groups and the
   // page write's seqs (the device pointers above are then unused); a decode
   // plan in compact form (plan_expand.h) has its ExpandDesc at ap_desc (> 0),

@@ -10,26 +10,20 @@ namespace {
 constexpr float kLn2 = 0.69314718055994531f;
 constexpr int kFewParts = 4;  // up to this many partials per row: combine_few_kernel
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// PER consecutive bf16 elements of a partial's O row, as fp32.
-template <int PER>
-__device__ __forceinline__ void load_part(const uint16_t* base, size_t elem, float (&v)[PER]) {
-  static_assert(PER == 2 || PER == 4, "two or four elements per lane");
-  if constexpr (PER == 4) {
-    const u32x2 w = *reinterpret_cast<const u32x2*>(base + elem);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      v[2 * i] = __uint_as_float(w[i] << 16);
-      v[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-    }
-  } else {
-    const uint32_t w = *reinterpret_cast<const uint32_t*>(base + elem);
-    v[0] = __uint_as_float(w << 16);
-    v[1] = __uint_as_float(w & 0xFFFF0000u);
+// N consecutive elements of the partials' O, as they are stored (bf16 or fp32) ...
+template <int N, bool F32>
+struct Raw {
+  typedef uint32_t words __attribute__((ext_vector_type(F32 ? N : N / 2)));
+  words w = words(0u);
+  __device__ __forceinline__ void load(const void* base, size_t elem) {
+    w = *reinterpret_cast<const words*>(static_cast<const uint8_t*>(base) + elem * (F32 ? 4 : 2));
   }
-}
+  // ... and element e as fp32.
+  __device__ __forceinline__ float operator[](int e) const {
+    if constexpr (F32) return __uint_as_float(w[e]);
+    else return __uint_as_float(e % 2 ? w[e / 2] & 0xFFFF0000u : w[e / 2] << 16);
+  }
+};
 
 // The merge group of workgroup block `grp`.
 template <int AP>
@@ -52,7 +46,7 @@ __device__ __forceinline__ CombineGroup group_of(const ExtendParams& p, const Pl
 // Few partials per row (at most kFewParts): a workgroup of 256 lanes covers 8 rows of
 // 32 lanes, and every load is issued before the first use, so a row waits for one
 // memory latency instead of one per partial.  Traffic bound for the extends.
-template <int D, int AP>
+template <int D, bool F32, int AP>
 __global__ __launch_bounds__(256) void combine_few_kernel(ExtendParams p, PlanArg<AP> ap) {
   constexpr int ROWS = 8;
   constexpr int PER = D / 32;  // dims per lane
@@ -61,19 +55,18 @@ __global__ __launch_bounds__(256) void combine_few_kernel(ExtendParams p, PlanAr
   const int lr = (blockIdx.x % wg_per_group) * ROWS + threadIdx.x / 32;
   if (lr >= cg.rows) return;
   const int d0 = (threadIdx.x % 32) * PER;
-  float mc[kFewParts], lc[kFewParts], oc[kFewParts][PER];
+  float mc[kFewParts], lc[kFewParts];
+  Raw<PER, F32> oc[kFewParts];
 #pragma unroll
   for (int c = 0; c < kFewParts; ++c) {
     mc[c] = -INFINITY;
     lc[c] = 0.f;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) oc[c][e] = 0.f;
     if (c < cg.n_parts) {
       const size_t pr = size_t(cg.part0 + c) * p.part_rows + lr;
       const float2 ml = *reinterpret_cast<const float2*>(p.part_ml + pr * 2);
       mc[c] = ml.x;
       lc[c] = ml.y;
-      load_part<PER>(p.part_o, pr * D + d0, oc[c]);
+      oc[c].load(p.part_o, pr * D + d0);
     }
   }
   float m = -INFINITY, L = 0.f, acc[PER];
@@ -109,7 +102,7 @@ __global__ __launch_bounds__(256) void combine_few_kernel(ExtendParams p, PlanAr
 // 94 partials) 94.5 -> 89.4 us; of 1700 keys (32 rows of 27) 11.9 -> 10.2 us of GPU
 // time; 48 decodes over fp8 pages (1536 rows of up to 33) 277.5 -> 277.0 us, with
 // batches of 8 278.2.
-template <int D, int kBatch, int AP>
+template <int D, int kBatch, bool F32, int AP>
 __global__ __launch_bounds__(256) void combine_many_kernel(ExtendParams p, PlanArg<AP> ap) {
   constexpr int LANES = D / 8, SLICES = 256 / LANES;
   __shared__ float sh_o[SLICES][D];
@@ -123,16 +116,15 @@ __global__ __launch_bounds__(256) void combine_many_kernel(ExtendParams p, PlanA
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
   for (int c0 = slice; c0 < cg.n_parts; c0 += kBatch * SLICES) {
     float2 ml[kBatch];
-    u32x4 oc[kBatch];
+    Raw<8, F32> oc[kBatch];
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
       const int c = c0 + k * SLICES;
       ml[k] = make_float2(-INFINITY, 0.f);
-      oc[k] = u32x4{0u, 0u, 0u, 0u};
       if (c < cg.n_parts) {
         const size_t pr = size_t(cg.part0 + c) * p.part_rows + lr;
         ml[k] = *reinterpret_cast<const float2*>(p.part_ml + pr * 2);
-        oc[k] = *reinterpret_cast<const u32x4*>(p.part_o + pr * D + d0);
+        oc[k].load(p.part_o, pr * D + d0);
       }
     }
     float m_new = m;
@@ -147,10 +139,7 @@ __global__ __launch_bounds__(256) void combine_many_kernel(ExtendParams p, PlanA
       const float w = c0 + k * SLICES < cg.n_parts ? __builtin_amdgcn_exp2f(ml[k].x - m_new) : 0.f;
       L += w * ml[k].y;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += w * __uint_as_float(oc[k][e] << 16);
-        acc[2 * e + 1] += w * __uint_as_float(oc[k][e] & 0xFFFF0000u);
-      }
+      for (int e = 0; e < 8; ++e) acc[e] += w * oc[k][e];
     }
     m = m_new;
   }
@@ -190,7 +179,7 @@ hipError_t launch_combine(const ExtendParams& p, int head_dim, int max_parts, hi
   const bool many = max_parts > kFewParts;
   const int rows_per_wg = many ? 1 : 8;
   const dim3 grid(p.n_groups * ((p.part_rows + rows_per_wg - 1) / rows_per_wg));
-#define CW_COMBINE(K_, ...)                                                                            \
+#define CW_COMBINE_AP(K_, ...)                                                                         \
   do {                                                                                                 \
     if (ap && ap->small())                                                                             \
       hipLaunchKernelGGL((K_<__VA_ARGS__, kPlanInSmallArgs>), grid, dim3(256), 0, stream, p, ap->small_plan()); \
@@ -198,6 +187,11 @@ hipError_t launch_combine(const ExtendParams& p, int head_dim, int max_parts, hi
       hipLaunchKernelGGL((K_<__VA_ARGS__, kPlanInArgs>), grid, dim3(256), 0, stream, p, ap->plan);              \
     else                                                                                               \
       hipLaunchKernelGGL((K_<__VA_ARGS__, kPlanInMemory>), grid, dim3(256), 0, stream, p, NoArgPlan{});         \
+  } while (0)
+#define CW_COMBINE(K_, ...)                                  \
+  do {                                                       \
+    if (p.part_f32) CW_COMBINE_AP(K_, __VA_ARGS__, true);    \
+    else CW_COMBINE_AP(K_, __VA_ARGS__, false);              \
   } while (0)
   if (head_dim == 64) {
     if (max_parts > 128) CW_COMBINE(combine_many_kernel, 64, 8);
@@ -211,6 +205,7 @@ hipError_t launch_combine(const ExtendParams& p, int head_dim, int max_parts, hi
     return hipErrorInvalidValue;
   }
 #undef CW_COMBINE
+#undef CW_COMBINE_AP
   return hipGetLastError();
 }
 

@@ -240,7 +240,10 @@ bool level_queues(const std::vector<Tile>& tiles, const std::vector<std::vector<
 // 4.16 -> 4.03 ms, a mixed fp8 step 5.53 -> 5.34 ms, 10 replies of 12-600 tokens
 // 744 -> 686 us, 4 prompts of 2-6k tokens without a prefix 365 -> 343 us (order
 // alone).  The gain is about half of what the model says: workgroups that share
-// the chip with idle CUs run faster.
+// the chip with idle CUs run faster.  The pieces' partials are fp32 (their sums would
+// stay in registers without the cut): rounded to bf16 they raised the error of 10
+// replies against 64 bits by 1%, and in fp32 the times are the same (10 replies 688
+// against 693 us, the mixed steps within 2%).
 void level_plan(ExtendPlan& plan, const std::vector<Tile>& tiles, const std::vector<Bundle>& whole_bundles,
                 int64_t wgt, int64_t R, int32_t head_dim, std::vector<std::vector<WorkItem>>& queues) {
   const size_t X = queues.size();
@@ -346,10 +349,16 @@ void level_plan(ExtendPlan& plan, const std::vector<Tile>& tiles, const std::vec
       for (const auto& q : pieces)
         for (const Piece& p : q) ++n_of[p.tile];
       int64_t n_parts = 0;
-      for (const int32_t n : n_of) n_parts += n > 1 ? n : 0;
+      size_t n_cut = 0;
+      for (const int32_t n : n_of) {
+        n_parts += n > 1 ? n : 0;
+        n_cut += n > 1 ? 1 : 0;
+      }
       const int64_t then = level + kMergeCost + kMergePartCost * n_parts;
-      const int64_t slot_bytes = int64_t(plan.part_rows) * (head_dim * 2 + 8);
-      cut = then * 103 < best * 100 && best - then >= kMinCutGain && n_parts * slot_bytes <= kLevelPartBytes;
+      const int64_t slot_bytes = int64_t(plan.part_rows) * (head_dim * 4 + 8);
+      const int64_t total_bytes =
+          static_cast<int64_t>(plan_meta_bytes(plan.seqs.size(), launch_count(pieces), n_cut)) + n_parts * slot_bytes;
+      cut = then * 103 < best * 100 && best - then >= kMinCutGain && total_bytes <= kLevelTotalBytes;
     }
   }
   if (!cut && !reorder) return;
@@ -364,6 +373,7 @@ void level_plan(ExtendPlan& plan, const std::vector<Tile>& tiles, const std::vec
   if (plan_meta_bytes(plan.seqs.size(), launch_count(pieces), n_groups) > plan.whole_meta_bytes + kLevelMetaBytes) return;
 
   // partial slots: a tile's pieces in key order
+  plan.part_f32 = true;
   plan.groups.clear();
   plan.n_parts = 0;
   std::vector<int32_t> part0(tiles.size(), -1);
@@ -610,8 +620,9 @@ void layout_workspace(ExtendPlan& plan, int32_t head_dim) {
   plan.meta_bytes = align256(plan.off_groups + plan.groups.size() * sizeof(CombineGroup));
   for (const CombineGroup& g : plan.groups) plan.max_parts = std::max(plan.max_parts, g.n_parts);
   plan.off_part_o = plan.meta_bytes;
-  // the partial O is stored in bf16 (2 bytes), the running max and sum in fp32
-  plan.off_part_ml = align256(plan.off_part_o + size_t(plan.n_parts) * plan.part_rows * head_dim * 2);
+  // the partial O in fp32 or bf16, the running max and sum in fp32
+  plan.off_part_ml =
+      align256(plan.off_part_o + size_t(plan.n_parts) * plan.part_rows * head_dim * (plan.part_f32 ? 4 : 2));
   plan.total_bytes = align256(plan.off_part_ml + size_t(plan.n_parts) * plan.part_rows * 2 * sizeof(float));
 }
 }  // namespace
@@ -643,7 +654,11 @@ std::pair<int64_t, int64_t> decode_counts(const int32_t* prefix_lens, int32_t nu
 // (48 decodes over fp8 pages: 6464 items 278 us, 7400 items 280 us).  Where more than
 // half of the items are the last, shorter chunks of their sequences, no chunk length
 // makes them even, and `plain` stays (96 prefixes of 200-6000 keys, 64-wide heads: 107 us
-// with it, 111-117 us with 1100-1500 items).
+// with it, 111-117 us with 1100-1500 items).  The figures are from bf16 partials; those
+// of an adjusted plan are fp32 (ExtendPlan::part_f32), which takes up to 2.7 us more and
+// leaves it ahead of the plain chunk: 8 bf16 prefixes of 2k-32k 100.3 us plain, 94.2 us
+// adjusted with bf16 partials, 96.5 us with fp32 ones; 16 of 1k-16k 99.9, 91.8, 93.9 us;
+// fp8, 24 of 3k-20k 106.4, 100.0, 102.7 us.
 int64_t round_chunk(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv_heads, int64_t unit,
                     int64_t max_chunk, int64_t min_chunk, int64_t num_cus, int64_t waves_per_cu, int64_t plain) {
   auto items = [&](int64_t chunk) { return decode_counts(prefix_lens, num_seqs, num_kv_heads, chunk).first; };
@@ -738,6 +753,7 @@ ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32
     return (a.kv_end - a.kv_begin) > (c.kv_end - c.kv_begin);
   });
   plan.items.insert(plan.items.end(), tails.begin(), tails.end());
+  plan.part_f32 = chunk != plain_chunk;
   layout_workspace(plan, head_dim);
   plan.whole_meta_bytes = plan.meta_bytes;
   if (chunk != plain_chunk) {

@@ -13,11 +13,11 @@ namespace cw {
 
 // Plans of at most kMaxLevelTiles query tiles may be levelled (tiles cut into key
 // ranges so that all workgroups finish together; longer work lists are level
-// enough whole), with at most kLevelPartBytes of partial slots (so that the plan
-// fits the library's static scratch array) and a meta of at most kLevelMetaBytes
-// more than the plan would have had otherwise.
+// enough whole), if meta and partial slots then take at most kLevelTotalBytes (the
+// library's static scratch array) and the meta at most kLevelMetaBytes more than
+// the plan would have had otherwise.
 constexpr int64_t kMaxLevelTiles = 4096;
-constexpr int64_t kLevelPartBytes = int64_t(48) << 20;
+constexpr int64_t kLevelTotalBytes = int64_t(64) << 20;
 constexpr size_t kLevelMetaBytes = size_t(64) << 10;
 
 struct Tuning {
@@ -46,6 +46,10 @@ struct ExtendPlan {
   size_t whole_meta_bytes = 0;
   size_t total_bytes = 0;
   int32_t part_rows = 0;  // rows per partial slot
+  // The partial O is fp32 where levelling or whole rounds chose the cuts: sums that a
+  // plan without them holds in one item's registers are not rounded on the way to the
+  // merge.  Other plans store it in bf16.
+  bool part_f32 = false;
   // decode plans: the same items and groups in compact form (see plan_expand.h)
   bool compact = false;
   std::vector<DecodeRec> recs;

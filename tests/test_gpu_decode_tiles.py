@@ -87,3 +87,21 @@ def test_merge_counts(d, p, parts):
         _check(lp, 2, 5, d, p, "bf16", 113, f"merge of {parts} partials d={d}")
     finally:
         cwlib.set_tuning(0, 0)
+
+
+# chunks adjusted to whole rounds, whose partials are fp32: up to 64 partials per row and more
+@pytest.mark.parametrize("d,p,dt,hkv,lp,parts", [
+    (128, 16, "bf16", 8, [63, 92, 85, 47, 151, 58, 93, 58, 277, 226, 456, 744, 658, 169, 321, 306, 108, 149, 178, 83,
+                          320, 66, 826], 9),
+    (128, 16, "bf16", 3, [3164, 9422, 3720], 99),
+    (64, 16, "bf16", 1, [33655, 31493, 56186, 4413, 21483], 220),
+    (64, 64, "fp8", 8, [1216, 490, 955, 85, 1205, 1209, 71, 102, 1291, 771, 164, 783, 222, 748, 1182, 1228, 703, 248, 158,
+                        357, 766, 1289], 7),
+])
+def test_merge_of_fp32_partials(d, p, dt, hkv, lp, parts):
+    print(f"\n[case] merge of fp32 partials d={d} {dt} up to {parts}", flush=True)
+    items, groups = cwlib.decode_plan(lp, hkv, 4, d, p, dt)
+    assert groups[:, 5].max() == parts
+    n_parts = int((items[:, 5] >= 0).sum())
+    assert cwlib.decode_workspace_bytes(lp, hkv, 4, d, p, dt) >= n_parts * 4 * d * 4
+    _check(lp, hkv, 4, d, p, dt, 137, f"merge of fp32 partials d={d} {dt} up to {parts}")

@@ -50,6 +50,17 @@ def test_levelled_against_whole_tiles(name):
     finally:
         cwlib.set_tuning(1, 0)
     assert (bits(out) != bits(whole)).any()  # another plan ran
+    if name == "equal_cost":
+        # the cuts cost no precision: over the cut tiles' rows the error is the whole tiles' (2% is
+        # far above its scatter over 10^5 values, partials rounded to bf16 would add 4 to 9%)
+        parts = items[items[:, 5] >= 0]
+        cut = np.zeros(out.shape[:2], bool)
+        cu = np.concatenate([[0], np.cumsum(c["ls"])])
+        for seq, kvh in np.unique(parts[:, :2], axis=0):  # (every sequence is one tile per kv head)
+            cut[cu[seq]:cu[seq + 1], kvh * c["g"]:(kvh + 1) * c["g"]] = True
+        rms = [np.sqrt(np.mean((as_f64(x) - ref)[cut] ** 2)) for x in (out, whole)]
+        print(f"rms error over {int(cut.sum())} cut rows: {rms[0]:.4e}, whole tiles {rms[1]:.4e}", flush=True)
+        assert rms[0] <= 1.02 * rms[1]
     assert_within_bf16_ulps(as_f64(out), as_f64(whole), 2, f"levelled {name}")
     # the rounded weights of a key range depend on its first tile's max: 2 * 2^-9 in lse
     assert_close(lse.cpu().double().numpy(), whole_lse.cpu().double().numpy(), 2 ** -8, None, f"levelled {name} lse")

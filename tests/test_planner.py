@@ -220,6 +220,42 @@ def test_levelled_plan_tiles_of_equal_cost_generated(hkv):
     assert cut >= 6
 
 
+def part_elem_bytes(total, n_seqs, items, n_groups, rows, d):
+    """Bytes per element of the partial O in a workspace of `total` bytes."""
+    up = lambda x: -(-x // 256) * 256
+    n_parts = int((items[:, 5] >= 0).sum())
+    meta = up(up(up(n_seqs * 16) + len(items) * 32) + n_groups * 32)
+    for e in (2, 4):
+        if up(up(meta + n_parts * rows * d * e) + n_parts * rows * 8) == total:
+            return e
+    raise AssertionError(total)
+
+
+@pytest.mark.parametrize("lp,ls,hkv,g,d,elem", [
+    ([20000] * 33, [64] * 33, 8, 4, 128, 4),  # tiles of one item each without levelling
+    ([30000] * 9, [300] * 9, 8, 4, 64, 4),
+    ([16384], [1024], 8, 4, 128, 2),  # cut because there are fewer tiles than CUs
+])
+def test_levelled_partials_are_fp32(lp, ls, hkv, g, d, elem):
+    """A sum that one item would hold in fp32 is not rounded to bf16 because levelling
+    cuts it."""
+    items = check_plan(np.array(lp), np.array(ls), hkv, g, d)
+    groups = len(np.unique(items[items[:, 5] >= 0][:, :3], axis=0))
+    total = cwlib.extend_workspace_bytes(lp, ls, hkv, g, d, 16)
+    assert part_elem_bytes(total, len(lp), items, groups, BM, d) == elem
+
+
+@pytest.mark.parametrize("lp,hkv,d,dt,elem", [
+    ([20000] * 8, 8, 128, "bf16", 4),  # whole rounds: other chunks than the mean's
+    ([300] * 30 + [30000] * 6, 8, 64, "fp8", 4),
+    ([1700], 8, 128, "bf16", 2), ([30000] * 40, 8, 128, "bf16", 2),  # the chunks they would have anyway
+])
+def test_decode_partials_of_adjusted_chunks_are_fp32(lp, hkv, d, dt, elem):
+    items, groups = cwlib.decode_plan(lp, hkv, 4, d, 16, dt)
+    total = cwlib.decode_workspace_bytes(lp, hkv, 4, d, 16, dt)
+    assert part_elem_bytes(total, len(lp), items, len(groups), 4, d) == elem
+
+
 RAGGED = [100 + 9 * i for i in range(100)]
 _MEAN = -(-sum((x + 32) // 32 * 8 for x in RAGGED) // 768) * 32  # keys of one of 768 equal shares (below 64 pages)
 N_RAGGED = sum((x + _MEAN) // _MEAN * 8 for x in RAGGED)
