@@ -518,6 +518,20 @@ int64_t sum_suffix(const int32_t* ls, int32_t num_seqs) {
   return t;
 }
 
+// What a plan is made from besides the call's own lengths and options, read once per
+// call: another thread may change the tuning at any time, and the parts of a plan (and
+// the key it is kept under) come from the same values.
+struct PlanEnv {
+  Tuning tuning;
+  int32_t cus = 256, xcds = 8;
+};
+PlanEnv plan_env() {
+  PlanEnv e;
+  e.tuning = current_tuning();
+  device_shape(&e.cus, &e.xcds);
+  return e;
+}
+
 // The last plan this thread made of each kind.  The layers of a model call with the
 // same lengths one after the other, and a workspace query asks for the plan of the
 // call that follows it: planning 300 to 2000 work items takes 25-130 us of host
@@ -531,16 +545,15 @@ class LastPlan {
   template <class Make, class Bytes>
   std::shared_ptr<const Plan> get(const int32_t* lp, const int32_t* ls, int32_t num_seqs,
                                   std::initializer_list<int32_t> options, Make&& make, Bytes&& bytes) {
-    int32_t cus = 256, xcds = 8;
-    device_shape(&cus, &xcds);
-    const Tuning t = current_tuning();
+    const PlanEnv env = plan_env();
+    const Tuning& t = env.tuning;
     key_.clear();
     key_.insert(key_.end(), options);
-    key_.insert(key_.end(), {num_seqs, cus, xcds, t.kv_chunk_tiles, t.target_wgs, t.deal_rounds, t.suffix_weight});
+    key_.insert(key_.end(), {num_seqs, env.cus, env.xcds, t.kv_chunk_tiles, t.target_wgs, t.deal_rounds, t.suffix_weight});
     key_.insert(key_.end(), lp, lp + num_seqs);
     if (ls != nullptr) key_.insert(key_.end(), ls, ls + num_seqs);
     if (plan_ && key_ == kept_) return plan_;
-    std::shared_ptr<const Plan> p = std::make_shared<const Plan>(make());
+    std::shared_ptr<const Plan> p = std::make_shared<const Plan>(make(env));
     if (bytes(*p) + key_.size() * sizeof(int32_t) <= kMaxKeptPlanBytes) {
       plan_ = p;
       kept_.swap(key_);
@@ -559,42 +572,41 @@ size_t kept_bytes(const ExtendPlan& p) {
 // Both pool dtypes run the LDS-staged kernel with the same row block
 // (LDS_BLOCK_M rows per work item, one workgroup per CU), so the extend plan
 // does not depend on the pool dtype.
-ExtendPlan make_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs, int32_t num_kv_heads,
-                     int32_t gqa_group, int32_t head_dim, const int32_t* cu_rows = nullptr,
+ExtendPlan make_plan(const PlanEnv& env, const int32_t* lp, const int32_t* ls, int32_t num_seqs,
+                     int32_t num_kv_heads, int32_t gqa_group, int32_t head_dim, const int32_t* cu_rows = nullptr,
                      const int32_t* bt_rows = nullptr) {
-  int32_t cus = 256, xcds = 8;
-  device_shape(&cus, &xcds);
   return build_extend_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim, LDS_BLOCK_M, 1,
-                           cus, xcds, current_tuning(), cu_rows, bt_rows);
+                           env.cus, env.xcds, env.tuning, cu_rows, bt_rows);
 }
 
 // Decode plans follow the pool dtype's tile length and residency (three
 // 16 KB-tile waves per CU for bf16, six 8 KB-tile waves for fp8).
-ExtendPlan make_decode_plan(const int32_t* lp, int32_t num_seqs, int32_t num_kv_heads,
+ExtendPlan make_decode_plan(const PlanEnv& env, const int32_t* lp, int32_t num_seqs, int32_t num_kv_heads,
                             int32_t gqa_group, int32_t head_dim, int32_t page_size,
                             cw_kv_dtype_t kv_dtype, const int32_t* cu_rows = nullptr,
                             const int32_t* bt_rows = nullptr) {
-  int32_t cus = 256, xcds = 8;
-  device_shape(&cus, &xcds);
   const bool fp8 = kv_dtype == CW_KV_FP8_E4M3FN;
   return build_decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size,
-                           decode_keys_per_tile(head_dim, fp8), decode_waves_per_cu(fp8), cus,
-                           current_tuning(), cu_rows, bt_rows);
+                           decode_keys_per_tile(head_dim, fp8), decode_waves_per_cu(fp8), env.cus,
+                           env.tuning, cu_rows, bt_rows);
 }
 
 std::shared_ptr<const ExtendPlan> extend_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs,
                                               int32_t num_kv_heads, int32_t gqa_group, int32_t head_dim) {
   thread_local LastPlan<ExtendPlan> last;
   return last.get(lp, ls, num_seqs, {num_kv_heads, gqa_group, head_dim},
-                  [&]() { return make_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim); }, kept_bytes);
+                  [&](const PlanEnv& env) {
+                    return make_plan(env, lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim);
+                  },
+                  kept_bytes);
 }
 std::shared_ptr<const ExtendPlan> decode_plan(const int32_t* lp, int32_t num_seqs, int32_t num_kv_heads,
                                               int32_t gqa_group, int32_t head_dim, int32_t page_size,
                                               cw_kv_dtype_t kv_dtype) {
   thread_local LastPlan<ExtendPlan> last;
   return last.get(lp, nullptr, num_seqs, {num_kv_heads, gqa_group, head_dim, page_size, int32_t(kv_dtype)},
-                  [&]() {
-                    return make_decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+                  [&](const PlanEnv& env) {
+                    return make_decode_plan(env, lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
                   },
                   kept_bytes);
 }
@@ -613,8 +625,8 @@ struct StepPlan {
 
 size_t align256h(size_t x) { return (x + 255) & ~size_t(255); }
 
-StepPlan make_step_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs, int32_t num_kv_heads,
-                        int32_t gqa_group, int32_t head_dim, int32_t page_size, cw_kv_dtype_t kv_dtype) {
+StepPlan make_step_plan(const PlanEnv& env, const int32_t* lp, const int32_t* ls, int32_t num_seqs,
+                        int32_t num_kv_heads, int32_t gqa_group, int32_t head_dim, int32_t page_size, cw_kv_dtype_t kv_dtype) {
   StepPlan sp;
   std::vector<int32_t> lp_e, ls_e, cu_e, lp_d, cu_d;
   int32_t cu = 0;
@@ -633,10 +645,10 @@ StepPlan make_step_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs, 
     cu += ls[b];
   }
   if (!sp.ext.empty())
-    sp.ext_plan = make_plan(lp_e.data(), ls_e.data(), static_cast<int32_t>(sp.ext.size()), num_kv_heads,
+    sp.ext_plan = make_plan(env, lp_e.data(), ls_e.data(), static_cast<int32_t>(sp.ext.size()), num_kv_heads,
                             gqa_group, head_dim, cu_e.data(), sp.ext.data());
   if (!sp.dec.empty())
-    sp.dec_plan = make_decode_plan(lp_d.data(), static_cast<int32_t>(sp.dec.size()), num_kv_heads,
+    sp.dec_plan = make_decode_plan(env, lp_d.data(), static_cast<int32_t>(sp.dec.size()), num_kv_heads,
                                    gqa_group, head_dim, page_size, kv_dtype, cu_d.data(), sp.dec.data());
   sp.off_ext_meta = align256h(sp.seqs.size() * sizeof(SeqInfo));
   sp.off_dec_meta = sp.off_ext_meta + sp.ext_plan.meta_bytes;
@@ -652,8 +664,8 @@ std::shared_ptr<const StepPlan> step_plan(const int32_t* lp, const int32_t* ls, 
                                           int32_t page_size, cw_kv_dtype_t kv_dtype) {
   thread_local LastPlan<StepPlan> last;
   return last.get(lp, ls, num_seqs, {num_kv_heads, gqa_group, head_dim, page_size, int32_t(kv_dtype)},
-                  [&]() {
-                    return make_step_plan(lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+                  [&](const PlanEnv& env) {
+                    return make_step_plan(env, lp, ls, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
                   },
                   [](const StepPlan& p) {
                     return kept_bytes(p.ext_plan) + kept_bytes(p.dec_plan) + p.seqs.size() * 24;
@@ -1393,7 +1405,7 @@ int64_t cw_extend_plan_items(const int32_t* prefix_lens_h, const int32_t* suffix
     if (check_lens(prefix_lens_h, suffix_lens_h, num_seqs, 0, page_size, num_kv_heads, gqa_group,
                    head_dim, false) != CW_OK)
       return -1;
-    ExtendPlan plan = make_plan(prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim);
+    ExtendPlan plan = make_plan(plan_env(), prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim);
     const int64_t n = static_cast<int64_t>(plan.items.size());
     if (items_out) {
       for (int64_t i = 0; i < std::min(n, capacity); ++i) {
@@ -1421,7 +1433,7 @@ int64_t cw_decode_plan_items(const int32_t* prefix_lens_h, int32_t num_seqs, int
                    false) != CW_OK)
       return -1;
     const ExtendPlan plan =
-        make_decode_plan(prefix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+        make_decode_plan(plan_env(), prefix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
     if (rebuilt && (!plan.compact || plan.recs.empty())) return -1;
     const int64_t n = static_cast<int64_t>(plan.items.size()), ng = static_cast<int64_t>(plan.groups.size());
     for (int64_t i = 0; items_out && i < std::min(n, items_capacity); ++i) {

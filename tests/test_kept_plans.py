@@ -59,3 +59,42 @@ def test_lengths_changed_in_place():
     other = cwlib.step_workspace_bytes(lp, ls, 8, 4, 128, 16, "bf16")
     lp[0] = 4000
     assert cwlib.step_workspace_bytes(lp, ls, 8, 4, 128, 16, "bf16") == first != other
+
+
+def test_tuning_changed_while_planning():
+    """A plan is kept under the tuning it was made with, also when another thread changes
+    the tuning while it is being made: asked for again under the first tuning, the size is
+    that of the first tuning."""
+    rng = np.random.default_rng(139)
+    lp = rng.integers(1000, 60000, 600).astype(np.int32)
+    ls = np.where(np.arange(600) % 2 == 0, 1, rng.integers(2, 900, 600)).astype(np.int32)
+    ask = lambda n: cwlib.step_workspace_bytes(lp[:n], ls[:n], 2, 4, 128, 16, "bf16")
+    sizes = {}
+
+    def fresh(n):
+        sizes[n] = ask(n)
+
+    for n in range(60, 64):
+        t = threading.Thread(target=fresh, args=(n,))
+        t.start()
+        t.join()
+    stop = threading.Event()
+
+    def flip():
+        while not stop.is_set():
+            cwlib.set_tuning(0, 7)
+            cwlib.set_tuning(0, 0)
+
+    try:
+        for i in range(400):
+            n = 60 + i % 4
+            stop.clear()
+            t = threading.Thread(target=flip)
+            t.start()
+            ask(n)
+            stop.set()
+            t.join()
+            assert ask(n) == sizes[n], (i, n)
+    finally:
+        stop.set()
+        cwlib.set_tuning(0, 0)
