@@ -241,7 +241,7 @@ bool compact_upload(const ExtendPlan& plan, size_t at, CompactUpload* cu) {
   cu->desc.tail_off = static_cast<uint32_t>(cu->verbatim + plan.recs.size() * sizeof(DecodeRec));
   cu->desc.items_off = static_cast<uint32_t>(at + plan.off_items);
   cu->desc.groups_off = static_cast<uint32_t>(at + plan.off_groups);
-  cu->bytes = (size_t(cu->desc.tail_off) + plan.tails.size() * sizeof(int32_t) + 15) & ~size_t(15);
+  cu->bytes = compact_bytes(cu->verbatim, plan.recs.size(), plan.tails.size());
   return true;
 }
 
@@ -253,10 +253,6 @@ void fill_compact(const CompactUpload& cu, uint8_t* h, FillHead&& fill_head) {
   std::memcpy(h + cu.desc.rec_off, cp.recs.data(), cp.recs.size() * sizeof(DecodeRec));
   std::memcpy(h + cu.desc.tail_off, cp.tails.data(), cp.tails.size() * sizeof(int32_t));
 }
-
-// Whether the compact blob and its ExpandDesc (at byte cu.bytes) fit the
-// kernel arguments.
-bool compact_arg_fits(const CompactUpload& cu) { return cu.bytes + sizeof(ExpandDesc) <= kArgPlanBytes; }
 
 // Waits until every workgroup of the upload kernel that last read `s` has
 // reported its reads (the done words at the slot's end).  The host runs up to
@@ -301,7 +297,7 @@ cw_status_t stage_and_launch(size_t bytes, size_t whole_bytes, void* dst, hipStr
     // a captured launch keeps it by value); a decode plan in compact form, with
     // its ExpandDesc behind the records, else as it is
     if (compact != nullptr && compact->plan != nullptr) {
-      if (compact_arg_fits(*compact)) {
+      if (compact_arg_fits(compact->bytes)) {
         ArgPlanBuf ap;
         fill_compact(*compact, ap.plan.bytes, fill_head);
         std::memcpy(ap.plan.bytes + compact->bytes, &compact->desc, sizeof(ExpandDesc));
@@ -583,12 +579,12 @@ ExtendPlan make_plan(const PlanEnv& env, const int32_t* lp, const int32_t* ls, i
 // 16 KB-tile waves per CU for bf16, six 8 KB-tile waves for fp8).
 ExtendPlan make_decode_plan(const PlanEnv& env, const int32_t* lp, int32_t num_seqs, int32_t num_kv_heads,
                             int32_t gqa_group, int32_t head_dim, int32_t page_size,
-                            cw_kv_dtype_t kv_dtype, const int32_t* cu_rows = nullptr,
+                            cw_kv_dtype_t kv_dtype, size_t meta_at = 0, const int32_t* cu_rows = nullptr,
                             const int32_t* bt_rows = nullptr) {
   const bool fp8 = kv_dtype == CW_KV_FP8_E4M3FN;
   return build_decode_plan(lp, num_seqs, num_kv_heads, gqa_group, head_dim, page_size,
                            decode_keys_per_tile(head_dim, fp8), decode_waves_per_cu(fp8), env.cus,
-                           env.tuning, cu_rows, bt_rows);
+                           env.tuning, meta_at, cu_rows, bt_rows);
 }
 
 std::shared_ptr<const ExtendPlan> extend_plan(const int32_t* lp, const int32_t* ls, int32_t num_seqs,
@@ -647,11 +643,12 @@ StepPlan make_step_plan(const PlanEnv& env, const int32_t* lp, const int32_t* ls
   if (!sp.ext.empty())
     sp.ext_plan = make_plan(env, lp_e.data(), ls_e.data(), static_cast<int32_t>(sp.ext.size()), num_kv_heads,
                             gqa_group, head_dim, cu_e.data(), sp.ext.data());
-  if (!sp.dec.empty())
-    sp.dec_plan = make_decode_plan(env, lp_d.data(), static_cast<int32_t>(sp.dec.size()), num_kv_heads,
-                                   gqa_group, head_dim, page_size, kv_dtype, cu_d.data(), sp.dec.data());
   sp.off_ext_meta = align256h(sp.seqs.size() * sizeof(SeqInfo));
   sp.off_dec_meta = sp.off_ext_meta + sp.ext_plan.meta_bytes;
+  if (!sp.dec.empty())
+    sp.dec_plan = make_decode_plan(env, lp_d.data(), static_cast<int32_t>(sp.dec.size()), num_kv_heads,
+                                   gqa_group, head_dim, page_size, kv_dtype, sp.off_dec_meta, cu_d.data(),
+                                   sp.dec.data());
   sp.meta_bytes = sp.off_dec_meta + sp.dec_plan.meta_bytes;
   sp.off_ext_part = sp.meta_bytes;
   sp.off_dec_part = sp.off_ext_part + (sp.ext_plan.total_bytes - sp.ext_plan.meta_bytes);
@@ -807,7 +804,7 @@ cw_status_t extend_impl(const void* q, const void* k_new, const void* v_new, voi
     }
     return CW_OK;
   };
-  const bool arg_plan = arg_plans() && (decode ? compact && compact_arg_fits(cu) : true);
+  const bool arg_plan = arg_plans() && (decode ? compact && compact_arg_fits(cu.bytes) : true);
   return stage_and_launch(plan.meta_bytes, plan.whole_meta_bytes, ws, stream, [&](uint8_t* h) { pack_plan_meta(plan, h); },
                           launch, no_alloc, plan_direct(no_alloc), compact ? &cu : nullptr,
                           [&](uint8_t* h) { pack_plan_head(plan, h); }, arg_plan);
@@ -1028,7 +1025,7 @@ cw_status_t step_impl(const void* q, const void* k_new, const void* v_new, void*
     if (!sp.ext.empty()) pack_plan_meta(sp.ext_plan, h + sp.off_ext_meta);
   };
   const bool arg_plan =
-      arg_plans() && (sp.dec.empty() || (sp.ext.empty() && compact && compact_arg_fits(cu)));
+      arg_plans() && (sp.dec.empty() || (sp.ext.empty() && compact && compact_arg_fits(cu.bytes)));
   const size_t whole_bytes = sp.off_ext_meta + sp.ext_plan.whole_meta_bytes + sp.dec_plan.whole_meta_bytes;
   return stage_and_launch(sp.meta_bytes, whole_bytes, ws, stream, [&](uint8_t* h) {
     head(h);

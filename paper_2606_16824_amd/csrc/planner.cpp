@@ -697,7 +697,8 @@ int64_t round_chunk(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv
 ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv_heads,
                              int32_t gqa_group, int32_t head_dim, int32_t page_size,
                              int32_t keys_per_tile, int32_t waves_per_cu, int32_t num_cus,
-                             const Tuning& tuning, const int32_t* cu_rows, const int32_t* bt_rows) {
+                             const Tuning& tuning, size_t meta_at, const int32_t* cu_rows,
+                             const int32_t* bt_rows) {
   ExtendPlan plan;
   plan.part_rows = gqa_group;
   plan.seqs.resize(num_seqs);
@@ -722,6 +723,17 @@ ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32
     chunk = round_chunk(prefix_lens, num_seqs, num_kv_heads, unit, max_chunk,
                         std::max<int64_t>(unit, (2 * int64_t(keys_per_tile) + unit - 1) / unit * unit), num_cus,
                         waves_per_cu, plain_chunk);
+  if (chunk != plain_chunk) {
+    // a plan that would fit the kernel arguments stays there: it then needs neither an
+    // upload nor, when captured, any set-up (other chunks may end more sequences short)
+    auto fits = [&](int64_t c) {
+      size_t n_tails = 0;
+      for (int32_t b = 0; b < num_seqs; ++b) n_tails += (int64_t(prefix_lens[b]) + 1) % c != 0 ? 1 : 0;
+      return compact_arg_fits(
+          compact_bytes(meta_at + align256(size_t(num_seqs) * sizeof(SeqInfo)), size_t(num_seqs), n_tails));
+    };
+    if (!fits(chunk) && fits(plain_chunk)) chunk = plain_chunk;
+  }
   // Longest chunks first so that short tails fill in at the end: every chunk but
   // the last of a (sequence, kv head) has the full length, so the order is the
   // full-length chunks in build order, then the shorter last chunks by length

@@ -68,12 +68,20 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
                              int32_t num_cus, int32_t num_xcds, const Tuning& tuning,
                              const int32_t* cu_rows = nullptr, const int32_t* bt_rows = nullptr);
 
+// Bytes of a decode plan in compact form whose records start at byte `at`.
+inline size_t compact_bytes(size_t at, size_t n_seqs, size_t n_tails) {
+  return (at + n_seqs * sizeof(DecodeRec) + n_tails * sizeof(int32_t) + 15) & ~size_t(15);
+}
+// Whether a compact form and its ExpandDesc fit the kernel arguments.
+inline bool compact_arg_fits(size_t bytes) { return bytes + sizeof(ExpandDesc) <= kArgPlanBytes; }
+
 // Decode plan (every suffix length 1): one item per (sequence, kv head, key
-// chunk) with `gqa_group` rows; `keys_per_tile` is the decode kernel's tile.
+// chunk) with `gqa_group` rows; `keys_per_tile` is the decode kernel's tile.  The
+// plan's meta starts at byte `meta_at` of its call's.
 ExtendPlan build_decode_plan(const int32_t* prefix_lens, int32_t num_seqs, int32_t num_kv_heads,
                              int32_t gqa_group, int32_t head_dim, int32_t page_size,
                              int32_t keys_per_tile, int32_t waves_per_cu, int32_t num_cus,
-                             const Tuning& tuning, const int32_t* cu_rows = nullptr,
+                             const Tuning& tuning, size_t meta_at = 0, const int32_t* cu_rows = nullptr,
                              const int32_t* bt_rows = nullptr);
 
 // Serialises seqs, items and groups into `dst` (meta_bytes long) at their offsets.

@@ -34,6 +34,8 @@ CASES = {
     "decode_step_fp8": ("step", [5, 700, 2000, 33, 12000], [1, 1, 1, 1, 1], 2, 4, 128, 16, "fp8"),
     # 360 sequences: a compact plan of about 16 KB, the largest that fits the arguments
     "decode_360": ("decode", 360, None, 1, 4, 64, 16, "bf16"),
+    # 390 of whole chunks: in the arguments as long as their chunks are not adjusted
+    "decode_390_even": ("decode", [4095] * 390, None, 1, 4, 64, 16, "bf16"),
     "decode_400": ("decode", 400, None, 1, 4, 64, 16, "bf16"),
     "extend_bf16": ("extend", [700, 90, 3000], [150, 64, 300], 2, 4, 128, 16, "bf16"),
     "extend_step_fp8": ("step", [700, 0, 3000], [150, 64, 300], 2, 4, 128, 16, "fp8"),

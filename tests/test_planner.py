@@ -285,3 +285,13 @@ def test_decode_chunks_fill_rounds(lp, hkv, dt, lo, hi):
     assert len(set(full)) <= 1
     rebuilt, rebuilt_groups = cwlib.decode_plan(lp, hkv, 4, 128, 16, dt, rebuilt=True)
     assert np.array_equal(items, rebuilt) and np.array_equal(groups, rebuilt_groups)
+
+
+def test_decode_chunks_keep_the_plan_in_the_arguments():
+    """390 sequences of 4096 keys, all in whole chunks of 1024: 40 bytes per sequence, which
+    fit the kernel arguments.  Chunks of 832 would add a last chunk's 4 bytes to each
+    and fit no longer, so they are taken only from where neither fits."""
+    items, _ = cwlib.decode_plan([4095] * 390, 1, 4, 128, 16)
+    assert len(items) == 4 * 390 and np.all(items[:, 4] - items[:, 3] == 1024)
+    items, _ = cwlib.decode_plan([4095] * 420, 1, 4, 128, 16)
+    assert len(items) == 5 * 420
