@@ -553,6 +553,8 @@ class LastPlan {
     if (bytes(*p) + key_.size() * sizeof(int32_t) <= kMaxKeptPlanBytes) {
       plan_ = p;
       kept_.swap(key_);
+    } else {
+      std::vector<int32_t>().swap(key_);  // nor is its key
     }
     return p;
   }

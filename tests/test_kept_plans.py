@@ -1,6 +1,7 @@
 """The plan a thread keeps from its last call is used only for the very same lengths
 and options: workspace sizes asked for in a mixed order on one thread equal those
 asked for on threads of their own, which keep nothing (runs on the CPU)."""
+import ctypes
 import threading
 
 import numpy as np
@@ -98,3 +99,25 @@ def test_tuning_changed_while_planning():
     finally:
         stop.set()
         cwlib.set_tuning(0, 0)
+
+
+class _MallInfo(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_size_t) for n in ("arena", "ordblks", "smblks", "hblks", "hblkhd", "usmblks", "fsmblks",
+                                               "uordblks", "fordblks", "keepcost")]
+
+
+def test_nothing_stays_of_a_large_plan():
+    """A plan above 1 MB is not kept, and neither are the lengths it was compared by."""
+    libc = ctypes.CDLL(None)
+    libc.mallinfo2.restype = _MallInfo
+
+    def in_use():
+        m = libc.mallinfo2()
+        return m.uordblks + m.hblkhd
+
+    lp, ls = np.full(1 << 20, 5, np.int32), np.zeros(1 << 20, np.int32)
+    ls[0] = 3
+    cwlib.extend_workspace_bytes(lp[:4], ls[:4], 1, 4, 64, 16)
+    before = in_use()
+    assert cwlib.extend_workspace_bytes(lp, ls, 1, 4, 64, 16) > 1 << 24
+    assert in_use() - before < 1 << 20
