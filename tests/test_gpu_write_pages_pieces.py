@@ -58,33 +58,40 @@ def test_split(name, dt):
 
 def test_every_value_against_many_scales():
     """All 65536 bf16 values (infinities, NaNs, subnormals and both zeros among them),
-    each against 8 scales per page: every exponent from 2^-70 to 2^69, significands
-    at both ends and between, and a scale the quick quotient does not take."""
+    each against 128 K scales and 128 V scales, drawn anew for every pass and page:
+    exponents drawn from -70 to 69 (half of them from -12 to 2), significands at both
+    ends, between, and within 32 of the multiples of 2^20 that the quick quotient's
+    proof turns on; some of the scales are ones it does not take."""
     d, p, hkv, tokens = 64, 16, 8, 1024
     spec = cw.custom_spec([0], [tokens], num_kv_heads=hkv, gqa_group=1, head_dim=d, page_size=p, kv_dtype="fp8", seed=97)
     w = cw.materialize(spec)
     vals = torch.arange(65536, dtype=torch.int32).to(torch.int16).view(torch.bfloat16).view(tokens, 1, d)
     w.k_new.copy_(vals.expand(tokens, hkv, d))
     w.v_new.copy_(vals.flip(0).expand(tokens, hkv, d))
-    rng = np.random.default_rng(101)
-    n = w.k_scale.numel()
-    for t in (w.k_scale, w.v_scale):
-        sig = rng.choice([0, 1, 0x7FFFFF, 0x7FFFFE, 0x400000, 0x555555], size=n).astype(np.uint32)
-        sig = np.where(rng.random(n) < 0.5, sig, rng.integers(0, 1 << 23, size=n).astype(np.uint32))
-        exp = np.where(np.arange(n) % 2 == 0, rng.integers(115, 130, size=n), rng.integers(57, 197, size=n)).astype(np.uint32)
-        t.copy_(torch.from_numpy(((exp << 23) | sig).astype(np.uint32).view(np.float32).reshape(t.shape)))
     # a NaN quotient clamps to -448
     nan = torch.isnan(w.k_new.float()), torch.isnan(w.v_new.float())
     dw = to_gpu(w)
-    cwlib.kv_write_pages(dw.k_new, dw.v_new, dw.k_pool, dw.v_pool, dw.block_table, spec.prefix_lens, spec.suffix_lens,
-                         k_scale=dw.k_scale, v_scale=dw.v_scale)
-    torch.cuda.synchronize()
     bt = w.block_table[0, :tokens // p].long()
-    for pool, new, scale, bad in ((dw.k_pool, w.k_new, w.k_scale, nan[0]), (dw.v_pool, w.v_new, w.v_scale, nan[1])):
-        got = pool.cpu()[bt].transpose(1, 2).reshape(tokens, hkv, d)
-        s = scale[bt].repeat_interleave(p, 0)[:, :, None]
-        x = torch.where(bad, torch.tensor(-float("inf")), new.float()) / s  # IEEE fp32 on the CPU
-        want = x.clamp(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8)
-        diff = int((got != want).sum())
-        print(f"differing codes: {diff} of {got.numel()}", flush=True)
-        assert diff == 0
+    rng = np.random.default_rng(101)
+    n = w.k_scale.numel()
+    for i in range(16):
+        for t in (w.k_scale, w.v_scale):
+            tie = rng.integers(8, 16, size=n) * (1 << 20) + rng.integers(-32, 33, size=n)
+            kinds = [rng.choice([0, 1, 0x7FFFFF, 0x7FFFFE, 0x400000, 0x555555], size=n), rng.integers(0, 1 << 23, size=n),
+                     np.maximum(tie, 1 << 23) - (1 << 23)]
+            sig = np.choose(rng.integers(0, 3, size=n), kinds).astype(np.uint32)
+            exp = np.where(np.arange(n) % 2 == 0, rng.integers(115, 130, size=n), rng.integers(57, 197, size=n))
+            t.copy_(torch.from_numpy(((exp.astype(np.uint32) << 23) | sig).view(np.float32).reshape(t.shape)))
+        dw.k_scale.copy_(w.k_scale)
+        dw.v_scale.copy_(w.v_scale)
+        cwlib.kv_write_pages(dw.k_new, dw.v_new, dw.k_pool, dw.v_pool, dw.block_table, spec.prefix_lens,
+                             spec.suffix_lens, k_scale=dw.k_scale, v_scale=dw.v_scale)
+        torch.cuda.synchronize()
+        for pool, new, scale, bad in ((dw.k_pool, w.k_new, w.k_scale, nan[0]), (dw.v_pool, w.v_new, w.v_scale, nan[1])):
+            got = pool.cpu()[bt].transpose(1, 2).reshape(tokens, hkv, d)
+            s = scale[bt].repeat_interleave(p, 0)[:, :, None]
+            x = torch.where(bad, torch.tensor(-float("inf")), new.float()) / s  # IEEE fp32 on the CPU
+            want = x.clamp(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8)
+            diff = int((got != want).sum())
+            print(f"pass {i}: differing codes: {diff} of {got.numel()}", flush=True)
+            assert diff == 0
