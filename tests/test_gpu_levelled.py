@@ -44,6 +44,12 @@ def test_levelled_against_whole_tiles(name):
         ref, ref_lse = oracle.extend_attention_blocked(paged_inputs(w))
         assert_close(as_f64(out), ref, BF16_MAX_ABS, BF16_MEAN_ABS, "levelled " + name)
         assert_close(lse.cpu().double().numpy(), ref_lse, 1e-2, None, "levelled " + name + " lse")
+        cwlib.set_tuning(2, 2)  # the four-wave kernel runs the same plan
+        try:
+            four, _ = run_extend(dw)
+        finally:
+            cwlib.set_tuning(2, 0)
+        assert_close(as_f64(four), ref, BF16_MAX_ABS, BF16_MEAN_ABS, "levelled four-wave " + name)
     cwlib.set_tuning(1, 256)
     try:
         whole, whole_lse = run_extend(dw)
