@@ -1404,7 +1404,9 @@ int64_t cw_extend_plan_items(const int32_t* prefix_lens_h, const int32_t* suffix
     if (check_lens(prefix_lens_h, suffix_lens_h, num_seqs, 0, page_size, num_kv_heads, gqa_group,
                    head_dim, false) != CW_OK)
       return -1;
-    ExtendPlan plan = make_plan(plan_env(), prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim);
+    const std::shared_ptr<const ExtendPlan> kept =
+        extend_plan(prefix_lens_h, suffix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim);
+    const ExtendPlan& plan = *kept;
     const int64_t n = static_cast<int64_t>(plan.items.size());
     if (items_out) {
       for (int64_t i = 0; i < std::min(n, capacity); ++i) {
@@ -1431,8 +1433,9 @@ int64_t cw_decode_plan_items(const int32_t* prefix_lens_h, int32_t num_seqs, int
     if (check_lens(prefix_lens_h, ones.data(), num_seqs, 0, page_size, num_kv_heads, gqa_group, head_dim,
                    false) != CW_OK)
       return -1;
-    const ExtendPlan plan =
-        make_decode_plan(plan_env(), prefix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+    const std::shared_ptr<const ExtendPlan> kept =
+        decode_plan(prefix_lens_h, num_seqs, num_kv_heads, gqa_group, head_dim, page_size, kv_dtype);
+    const ExtendPlan& plan = *kept;
     if (rebuilt && (!plan.compact || plan.recs.empty())) return -1;
     const int64_t n = static_cast<int64_t>(plan.items.size()), ng = static_cast<int64_t>(plan.groups.size());
     for (int64_t i = 0; items_out && i < std::min(n, items_capacity); ++i) {

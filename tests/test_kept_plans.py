@@ -1,6 +1,7 @@
 """The plan a thread keeps from its last call is used only for the very same lengths
-and options: workspace sizes asked for in a mixed order on one thread equal those
-asked for on threads of their own, which keep nothing (runs on the CPU)."""
+and options: workspace sizes and work lists asked for in a mixed order on one thread
+equal those asked for on threads of their own, which keep nothing (runs on the CPU).
+The work list queries serve the kept plan, as the calls do."""
 import ctypes
 import threading
 
@@ -99,6 +100,38 @@ def test_tuning_changed_while_planning():
     finally:
         stop.set()
         cwlib.set_tuning(0, 0)
+
+
+def _on_own_thread(f):
+    got = []
+    t = threading.Thread(target=lambda: got.append(f()))
+    t.start()
+    t.join()
+    return got[0]
+
+
+def _same(a, b):
+    return all(x.shape == y.shape and np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def test_other_plans_of_the_same_size():
+    """Calls whose plans take the same bytes but hold other work (lengths permuted, moved
+    between sequences or changed within a key tile): each gets its own work list."""
+    exts = [([5000, 9000, 300], [400, 70, 900]), ([9000, 5000, 300], [400, 70, 900]), ([5000, 9000, 300], [70, 400, 900]),
+            ([5001, 9000, 300], [400, 70, 900]), ([5000, 9000, 300], [399, 71, 900])]
+    ask = [(lambda lp=lp, ls=ls: (cwlib.plan_items(lp, ls, 4, 8, 128, 16),)) for lp, ls in exts]
+    size = lambda lp, ls: cwlib.extend_workspace_bytes(lp, ls, 4, 8, 128, 16)
+    assert len({size(lp, ls) for lp, ls in exts}) < len(exts)
+    decs = [[5000, 9000, 300], [9000, 5000, 300], [5000, 300, 9000], [5001, 9000, 300], [4999, 9001, 300]]
+    ask += [(lambda lp=lp: cwlib.decode_plan(lp, 4, 8, 128, 16)) for lp in decs]
+    assert len({cwlib.decode_workspace_bytes(lp, 4, 8, 128, 16) for lp in decs}) < len(decs)
+    fresh = [_on_own_thread(f) for f in ask]
+    n = len(exts)
+    for group in (fresh[:n], fresh[n:]):
+        assert not any(_same(a, b) for i, a in enumerate(group) for b in group[:i])
+    rng = np.random.default_rng(149)
+    for i in rng.integers(0, len(ask), 200).tolist():
+        assert _same(ask[i](), fresh[i]), i
 
 
 class _MallInfo(ctypes.Structure):
