@@ -321,8 +321,10 @@ cw_status_t cw_check_block_table(const int32_t* block_table, int32_t bt_stride, 
  *                           equal shares of cost, where a 64-key tile that
  *                           reaches past the cached prefix costs value / 100
  *                           of a prefix tile (1 .. 10000; default 125, the
- *                           measured cost of the masked tiles; 100: equal
- *                           key counts).
+ *                           measured cost of a tile that straddles the prefix's
+ *                           end or the diagonal; tiles wholly among the new
+ *                           tokens that every row sees count the same, though
+ *                           they run like prefix tiles; 100: equal key counts).
  *   CW_TUNE_COMPACT_DECODE  1 = a decode plan (of cw_decode_attention or of a
  *                           step's decodes) is uploaded in compact form, one
  *                           record per sequence, and rebuilt on the device by

@@ -72,13 +72,17 @@ size_t launch_count(const std::vector<std::vector<T>>& queues) {
 // key tile when all its rows are in use (1.7-2.2 us at head dim 128).  Fewer
 // rows make a tile cheaper only down to the time its K/V take to arrive
 // (measured per tile, 256 workgroups, unshared K/V: 2.19 us with 256 rows, 1.94
-// with 192, 1.58 with 128, 1.53 with 32).
+// with 192, 1.58 with 128, 1.53 with 32).  At head dim 64 the same units stand for
+// about half that time.  A tile past the prefix counts suffix_weight: right for one
+// that straddles the prefix's end or the diagonal, too much for one wholly among the
+// new tokens, which the kernel runs without masks like a prefix tile.
 constexpr int64_t kItemCost = 300;       // start-up and epilogue of a work item
 constexpr int64_t kMergeCost = 450;      // the merge kernel's launch and latency
 constexpr int64_t kMergePartCost = 2;    // per partial slot merged
 constexpr int64_t kMinGap = MIN_CHUNK_TILES * 100 + kItemCost;
-// What cutting tiles has to gain at least (about 55 us): calls of 20-100 us lost
-// 5-60 us to the merge and the larger plan when they were levelled.
+// What cutting tiles has to gain at least (about 55 us at head dim 128): calls of
+// 20-100 us lost 5-60 us to the merge and the larger plan when they were levelled.
+// Asked in full also of plans that have partials, and so a merge, already.
 constexpr int64_t kMinCutGain = 3000;
 
 int64_t row_rate(int32_t rows) {
@@ -489,9 +493,9 @@ ExtendPlan build_extend_plan(const int32_t* prefix_lens, const int32_t* suffix_l
       }
       chunk_at.emplace_back(static_cast<int64_t>(first.size()), part0);
       // chunk boundaries: equal shares of the tile's cost, a key tile that
-      // reaches past the cached prefix (masked, read from the new tokens)
-      // costing suffix_weight / 100 of a prefix tile (forced chunk sizes:
-      // equal key counts); every chunk at least one tile long
+      // reaches past the cached prefix (read from the new tokens) counting
+      // suffix_weight / 100 of a prefix tile (forced chunk sizes: equal key
+      // counts); every chunk at least one tile long
       const int64_t n_pre = t.n_pre;
       const int64_t wgt = tuning.kv_chunk_tiles > 0 ? 100 : std::max(1, tuning.suffix_weight);
       const int64_t total_cost = n_pre * 100 + (t.n_kt - n_pre) * wgt;
